@@ -11,8 +11,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqgemm.so")
-SOURCES = [os.path.join(CSRC, "qgemm_api.hip")]
-DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("qgemm_kernels.hpp", "qgemm_aux.hpp", "qgemm_smallm.hpp", "attn_kernels.hpp")] + [
+SOURCES = [os.path.join(CSRC, f) for f in ("qgemm_api.hip", "moe_direct.hip")]
+DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("qgemm_kernels.hpp", "qgemm_aux.hpp", "qgemm_smallm.hpp", "moe_direct.hpp",
+                                                  "moe_direct_api.hpp", "attn_kernels.hpp")] + [
     os.path.join(os.path.dirname(HERE), "include", "qgemm.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -23,7 +24,6 @@ FLAGS = [
     "-O3",
     "-std=c++20",
     "-fPIC",
-    "-shared",
     # no packed-fp32 VALU instructions in any device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall",
@@ -32,14 +32,26 @@ FLAGS = [
 
 
 def build(verbose: bool = False, extra=None) -> str:
-    cmd = [HIPCC, *FLAGS, *(extra or []), *SOURCES, "-o", LIB + ".tmp"]
+    """Compile every source (side by side, one object each) and link the library."""
+    objs = [os.path.splitext(src)[0] + ".o" for src in SOURCES]
+    cmds = [[HIPCC, *FLAGS, *(extra or []), "-c", src, "-o", obj] for src, obj in zip(SOURCES, objs)]
+    link = [HIPCC, f"--offload-arch={ARCH}", "-shared", *objs, "-o", LIB + ".tmp"]
     if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    out = "\n".join(l for l in (res.stdout + res.stderr).splitlines()
-                    if "not a recognized feature" not in l)
-    if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{out}")
+        for cmd in [*cmds, link]:
+            print(" ".join(cmd), flush=True)
+    procs = [subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for cmd in cmds]
+    outs = [p.communicate()[0] for p in procs]
+    rcs = [p.returncode for p in procs]
+    if not any(rcs):
+        res = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        outs.append(res.stdout)
+        rcs.append(res.returncode)
+    out = "\n".join(l for l in "".join(outs).splitlines() if "not a recognized feature" not in l)
+    for obj in objs:
+        if os.path.exists(obj):
+            os.remove(obj)
+    if any(rcs):
+        raise RuntimeError(f"hipcc failed ({rcs}):\n{out}")
     if verbose and out.strip():
         print(out)
     os.replace(LIB + ".tmp", LIB)

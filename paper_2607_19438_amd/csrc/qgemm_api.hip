@@ -173,6 +173,27 @@ int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStr
   return check_launch("qgemm_dense (small M) split reduction");
 }
 
+// Eight-wave tiles with K split over S workgroups per tile: fp32 partials, summed in split order by a
+// second kernel. (Summing them in the tile's last workgroup instead, on arrival counters with
+// device-scope stores: Q4 512x8192x3072 40.1 -> 39.1 us, but Q4 768x1536x2048 22.6 -> 23.8, Q8
+// 300x5000x4096 28.7 -> 31.5 and 2048x2048x8192 83.9 -> 90.5, where few workgroups sum many partials.)
+template <int FMT, int BM, int BN>
+int launch_split(qg::TileArgs a, int S, const void* wq, const void* sc, hipStream_t s) {
+  if (S == 1) return launch_dense<FMT, BM, BN, 2, 4, 2>(a, wq, sc, s);
+  const long mn = (long)a.M * a.N;
+  std::lock_guard<std::mutex> lock(g_split_mutex);
+  float* ws = nullptr;
+  int rc = split_workspace((size_t)S * mn, &ws);
+  if (rc != QGEMM_OK) return rc;
+  a.ws = ws;
+  a.splits = S;
+  rc = launch_dense<FMT, BM, BN, 2, 4, 2>(a, wq, sc, s);
+  if (rc != QGEMM_OK) return rc;
+  const long n4 = mn / 4;
+  hipLaunchKernelGGL(qg::splitk_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, a.y, n4, S, mn);
+  return check_launch("qgemm_dense split-K reduction");
+}
+
 template <int FMT>
 int dense_dispatch(qg::TileArgs a, const void* wq, const void* sc, hipStream_t s) {
   if (a.M <= qg::kSmMaxM) return small_dispatch<FMT>(a, wq, sc, s);
@@ -189,51 +210,27 @@ int dense_dispatch(qg::TileArgs a, const void* wq, const void* sc, hipStream_t s
   const long big = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
   if (a.M >= 256 && a.N >= 256 && big >= 200) return launch_dense<FMT, 256, 256, 2, 4, 2>(a, wq, sc, s);
   const int nk = (a.K + 63) / 64;
-  // up to 1024 rows with few 256x256 tiles: 128x256 eight-wave tiles, twice the tiles, so half the
-  // K split and half the fp32 partials; the split keeps tiles x splits <= 256 (one round). Up to
-  // 2048 rows only where these tiles need no split. Measured against the 256x256 split: dense Q4
-  // 512x8192x3072 48-49 vs 51-53 us, Q8 512x2048x2048 26.6 vs 34.4, Q4 768x1536x2048 27.0 vs 35.6,
-  // Q8 256x8192x2048 29.2 vs 36.8, Q8 2048x4096x2048 49.6 vs 60.8, Q4 1536x4096x4096 78 vs 97 us;
-  // Q8 2048x2048x8192 (two splits needed) 100 vs 92.7 us stays on the 256x256 split.
-  const long t2 = (long)((a.M + 127) / 128) * ((a.N + 255) / 256);
+  // up to 1024 rows with few 256x256 tiles: eight-wave tiles of half that size, twice the tiles, so
+  // half the K split and half the fp32 partials; the split keeps tiles x splits <= 256 (one round).
+  // Up to 2048 rows only where these tiles need no split. From 256 rows on 256x128 (each weight is
+  // dequantised for 256 rows, not 128), below 128x256. Measured, 128x256 against 256x128: Q4
+  // 512x8192x3072 45.6 vs 40.1 us, 1024x4096x4096 50.9 vs 47.7, 768x1536x2048 25.5 vs 22.6,
+  // 1536x4096x4096 67.4 vs 60.4; Q8 512x2048x2048 24.0 vs 23.4, 2048x4096x2048 43.6 vs 41.4,
+  // 300x5000x4096 32.1 vs 28.7; and 256x128 against 256x256: Q8 2048x2048x8192 84.2 vs 83.9 (two
+  // splits against four), 2048x8192x2048 81 vs 69.7.
+  const bool tall = a.M >= 256;
+  const long t2 = tall ? (long)((a.M + 255) / 256) * ((a.N + 127) / 128) : (long)((a.M + 127) / 128) * ((a.N + 255) / 256);
   if (a.M >= 128 && a.N >= 256 && ((long)a.M * a.N) % 4 == 0 && (a.M <= 1024 || (a.M <= 2048 && t2 > 128))) {
     int S = (int)std::max<long>(1, std::min<long>(8, 256 / t2));
     while (S > 1 && nk / S < kMinStepsPerSplit) --S;
-    if (S == 1) return launch_dense<FMT, 128, 256, 2, 4, 2>(a, wq, sc, s);
-    const long mn = (long)a.M * a.N;
-    std::lock_guard<std::mutex> lock(g_split_mutex);
-    float* ws = nullptr;
-    int rc = split_workspace((size_t)S * mn, &ws);
-    if (rc != QGEMM_OK) return rc;
-    a.ws = ws;
-    a.splits = S;
-    rc = launch_dense<FMT, 128, 256, 2, 4, 2>(a, wq, sc, s);
-    if (rc != QGEMM_OK) return rc;
-    const long n4 = mn / 4;
-    hipLaunchKernelGGL(qg::splitk_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, a.y, n4, S,
-                       mn);
-    return check_launch("qgemm_dense split-K reduction");
+    return tall ? launch_split<FMT, 256, 128>(a, S, wq, sc, s) : launch_split<FMT, 128, 256>(a, S, wq, sc, s);
   }
-  // few 256x256 tiles but a long K: split K over several workgroups per tile (fp32 partials,
-  // summed in split order by a second kernel) so that every CU gets a 256x256 tile
+  // few 256x256 tiles but a long K: split K over several workgroups per tile so that every CU gets
+  // a 256x256 tile
   if (a.M >= 256 && a.N >= 256 && ((long)a.M * a.N) % 4 == 0) {
     int S = (int)std::min<long>(8, (256 + big - 1) / big);
     while (S > 1 && nk / S < kMinStepsPerSplit) --S;
-    if (S > 1) {
-      const long mn = (long)a.M * a.N;
-      std::lock_guard<std::mutex> lock(g_split_mutex);
-      float* ws = nullptr;
-      int rc = split_workspace((size_t)S * mn, &ws);
-      if (rc != QGEMM_OK) return rc;
-      a.ws = ws;
-      a.splits = S;
-      rc = launch_dense<FMT, 256, 256, 2, 4, 2>(a, wq, sc, s);
-      if (rc != QGEMM_OK) return rc;
-      const long n4 = mn / 4;
-      hipLaunchKernelGGL(qg::splitk_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, ws, a.y, n4, S,
-                         mn);
-      return check_launch("qgemm_dense split-K reduction");
-    }
+    if (S > 1) return launch_split<FMT, 256, 256>(a, S, wq, sc, s);
   }
   return launch_dense<FMT, 128, 128, 2, 2, 2>(a, wq, sc, s);
 }

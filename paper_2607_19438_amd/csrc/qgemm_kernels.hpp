@@ -206,7 +206,8 @@ struct TileKernel {
   static constexpr int kWChunkElems = (FMT == kQ8) ? 16 : 32;   // weights per 16-byte load
   static constexpr int kWChunksPerRow = kBK / kWChunkElems;     // 4 (Q8) or 2 (Q4)
   static constexpr int kWStepBytes = (FMT == kQ8) ? kBK : kBK / 2;   // packed bytes of one row per K step
-  static constexpr int kWChunks = BN * kWChunksPerRow / kThreads;
+  static constexpr int kWTotal = BN * kWChunksPerRow;            // 16-byte weight loads of a K step
+  static constexpr int kWChunks = kWTotal / kThreads;           // per thread (0: half of the threads take one each)
   static constexpr int kXTileBytes = BM * kRowBytes;
   static constexpr int kWTileBytes = BN * kRowBytes;
   static constexpr int kXStages = XS;                            // activation stages (DMA runs XS-1 steps ahead)
@@ -214,7 +215,7 @@ struct TileKernel {
   static constexpr int kLdsBytes = XS * kXTileBytes + 2 * kWTileBytes;
   static_assert(XS == 2 || XS == 3, "two or three activation stages");
   static_assert(kXLoads * kXWaves * 8 == BM, "x tile must split into 8-row groups per wave");
-  static_assert(kWChunks * kThreads == BN * kWChunksPerRow, "w tile must split evenly");
+  static_assert(kWChunks * kThreads == kWTotal || 2 * kWTotal == kThreads, "w tile must split evenly");
   static_assert(kTM >= 1 && kTN >= 1, "wave tile must hold a 32x32 block");
 };
 
@@ -354,11 +355,10 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, const uint8_t* __re
   // the K loop is unrolled over a period in which activation stage, weight register set and
   // weight LDS stage (two) all repeat
   constexpr int kPeriod = (XS == 3 || kWD == 3) ? 6 : (kWD == 4 ? 4 : 2);
-  static_assert(kUnits % 4 == 0, "units must spread evenly over the four K16 sub-steps");
   constexpr int kMfmaPerKK = KT::kTM * KT::kTN;
   constexpr int kValuPerUnit = (FMT == kQ8) ? 20 : 17;
 
-  // Ping-pong (8-wave tiles): the two waves sharing a SIMD belong to different wave rows (wm).
+  // Ping-pong (8-wave tiles 256, 192 or 128 rows high): the two waves sharing a SIMD belong to different wave rows (wm).
   // Per K step, wm = 1 waves issue the activation DMA while wm = 0 waves run their MFMAs; after
   // a barrier, wm = 1 waves run their MFMAs while wm = 0 waves load and dequantise the next
   // step's weights; a second barrier closes the step. One wave per SIMD issues MFMAs at a time,
@@ -374,12 +374,14 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, const uint8_t* __re
   // DMA role's phase is then the activation DMA and its fragment loads only): 488.7 vs 493.5 us
   // (T=8192 gate/up), 158.1 vs 164.2 us (T=2048 gate/up), same-box A/B; Q8 keeps its 3:1 split
   // (dense 0.8% slower with every chunk on one role)
-  constexpr int CQ = PP ? ((FMT == kQ4) ? 2 * KT::kWChunks
-                                                       : (KT::kWChunks >= 2 ? (3 * KT::kWChunks + 1) / 2 : KT::kWChunks))
-                        : KT::kWChunks;
-  constexpr int CD = PP ? 2 * KT::kWChunks - CQ : KT::kWChunks;
+  // Narrow tiles (BN = 128) have one (Q4) or two (Q8) chunks per thread of one role, which takes them
+  // all (256x128 Q8 2048x2048x8192 84.2 us, split 1:1 87.4).
+  constexpr int kWHalf = KT::kWTotal / (KT::kThreads / 2);        // chunks if one role took them all
+  constexpr int CQ = PP ? ((FMT == kQ4) ? kWHalf : (kWHalf >= 4 ? (3 * kWHalf / 2 + 1) / 2 : kWHalf)) : KT::kWChunks;
+  constexpr int CD = PP ? kWHalf - CQ : KT::kWChunks;
   constexpr int WC = CQ > CD ? CQ : CD;                           // register arrays sized for either role
-  static_assert(!PP || CQ + CD == 2 * KT::kWChunks, "every chunk dequantised once");
+  static_assert(PP || (KT::kWChunks > 0 && kUnits % 4 == 0),
+                "single-barrier tiles: whole chunks per thread, spread evenly over the K16 sub-steps");
   constexpr int kWStride = PP ? KT::kThreads / 2 : KT::kThreads;
   auto xstage_ptr = [&](int stage) { return (lds_char*)(stage == 0 ? st.x[0] : stage == 1 ? st.x[1] : st.x[2]); };
   auto wstage_ptr = [&](int stage) { return (lds_char*)(stage == 0 ? st.w[0] : st.w[1]); };

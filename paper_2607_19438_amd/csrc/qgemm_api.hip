@@ -331,8 +331,16 @@ int bucket_geometry(int n, int* chunk, int* nblk) {
 
 constexpr int kMaxE = 4096;
 
+// One workgroup buckets up to 4096 assignments over up to 512 experts (measured at bucket_small_kernel)
+bool bucket_small(int n, int E) { return n <= qg::kSmallSlots && E <= qg::kSmallExperts; }
+
 int enqueue_bucket(const int32_t* idx, const int32_t* offsets, int32_t* perm, int n, int E, int32_t* counts,
                    int32_t* flag, int seq, float* ypoison, int N, hipStream_t s) {
+  if (bucket_small(n, E)) {
+    hipLaunchKernelGGL(qg::bucket_small_kernel, dim3(1), dim3(64 * qg::kSmallWaves),
+                       (size_t)E * qg::kSmallWaves * sizeof(int32_t), s, idx, offsets, n, E, perm, flag, seq, ypoison, N);
+    return check_launch("moe bucket");
+  }
   int chunk, nblk;
   bucket_geometry(n, &chunk, &nblk);
   const size_t lds = (size_t)E * sizeof(int32_t);
@@ -444,7 +452,7 @@ int qgemm_moe_bucket(const int32_t* token_expert_idx, const int32_t* expert_offs
   if (!ws) return fail(QGEMM_EHIP, "hipGetDevice failed");
   int chunk, nblk;
   bucket_geometry(n_assign, &chunk, &nblk);
-  int rc = grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
+  int rc = bucket_small(n_assign, E) ? QGEMM_OK : grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
   if (rc != QGEMM_OK) return rc;
   size_t one = 0;
   if (ws->flag == nullptr) {
@@ -524,7 +532,7 @@ int qgemm_moe(const void* x, const int32_t* token_expert_idx, const int32_t* exp
     int chunk, nblk;
     bucket_geometry(n, &chunk, &nblk);
     rc = grow(&ws->perm, &ws->perm_cap, (size_t)n);
-    if (rc == QGEMM_OK) rc = grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
+    if (rc == QGEMM_OK && !bucket_small(n, E)) rc = grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
     if (rc == QGEMM_OK && ws->flag == nullptr) {
       size_t one = 0;
       rc = grow(&ws->flag, &one, 1);

@@ -16,6 +16,15 @@
 // Keys and values both go from HBM to LDS by DMA, with no register staging.
 // Rows are normalised by the running sum at the end and stored as bf16. Causal blocks above the
 // diagonal are skipped; blocks on it are masked key by key.
+//
+// SPLIT (few workgroups): the workgroup owns 64 query rows, and wave w takes rows 32 (w % 2) .. + 31
+// against the (w / 2)-th 32 keys of every block, so a query's keys are shared by two waves, each with its
+// own maximum, sum and output, merged through LDS at the end. With few workgroups the call lasts as long
+// as the chain of key blocks of its last query rows, walked by one wave per SIMD (0.69 blocks/us alone,
+// 0.95 for two waves together); the split halves the chain and doubles the workgroups, at more DMA, LDS
+// and barrier work per MFMA. Measured (unsplit -> split, us): causal 512 x 32/8 heads D=128 14.6 -> 11.1,
+// 4 x 300 x 8/8 10.4 -> 8.5, 3 x 700 x 32/8 D=64 18.3 -> 15.3, 2048 x 32/4 D=128 48.1 -> 46.8, 4096 x 32/4
+// 142 -> 155; not causal 2 x 1000 x 16/4 D=64 15.8 -> 14.8, 2048 x 32/4 D=128 66.8 -> 77.0.
 #pragma once
 
 #include "qgemm_kernels.hpp"
@@ -23,8 +32,9 @@
 namespace qg {
 
 constexpr int kAttnThreads = 256;   // four waves
-constexpr int kAttnBQ = 128;        // query rows per workgroup
 constexpr int kAttnBK = 64;         // keys per block
+template <bool SPLIT>
+constexpr int kAttnBQ = SPLIT ? 64 : 128;   // query rows per workgroup
 
 struct AttnArgs {
   const uint16_t* q;   // bf16 [B][S][H][D]
@@ -49,9 +59,11 @@ __device__ __forceinline__ float other_half(float x) {
   return __builtin_bit_cast(float, (unsigned)(lane < 32 ? r[1] : r[0]));
 }
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool SPLIT>
 __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   static_assert(D == 64 || D == 128, "head dimension 64 or 128");
+  constexpr int BQ = kAttnBQ<SPLIT>;
+  constexpr int NT = SPLIT ? 1 : 2;           // 32-key tiles of a block per wave
   constexpr int KCH = D / 8;                  // 16-byte chunks per key row
   constexpr int KSTEPS = D / 16;              // K16 steps of the score product
   constexpr int DT = D / 32;                  // 32-row tiles of O^T
@@ -70,9 +82,18 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   const int col = lane & 31;     // this lane's query within the wave (MFMA column)
   const int hh = lane >> 5;      // MFMA lane half
   const int S = a.S, H = a.H;
-  const int nqb = (S + kAttnBQ - 1) / kAttnBQ;
+  const int nqb = (S + BQ - 1) / BQ;
   int bh, qb;
-  if (CAUSAL) {
+  if (CAUSAL && SPLIT) {
+    // the heaviest query blocks of all heads first, so that light ones fill in. Workgroups reach the 8
+    // XCDs round-robin: with a multiple of 8 heads each XCD takes consecutive ones, which share keys and
+    // values in its L2
+    const int nbh = a.B * H;
+    const int L = (int)blockIdx.x;
+    qb = nqb - 1 - L / nbh;
+    const int i = L - (nqb - 1 - qb) * nbh;
+    bh = (nbh & 7) == 0 ? (i & 7) * (nbh >> 3) + (i >> 3) : i;
+  } else if (CAUSAL) {
     // heavy members (query blocks nqb-1 .. nqb-ceil(nqb/2)) of all heads first, then the light
     // members in the same order: workgroups L and L + (heavy count) are complementary
     const int hi = (nqb + 1) >> 1;
@@ -95,8 +116,10 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   const int b = bh / H;
   const int h = bh - b * H;
   const int g = h / (H / a.Hkv);
-  const int q0 = qb * kAttnBQ;
-  const int qrow = q0 + wave * 32 + col;      // this lane's query position
+  const int q0 = qb * BQ;
+  const int kh = SPLIT ? wave >> 1 : 0;       // first 32-key tile of a block
+  const int qs = q0 + (SPLIT ? wave & 1 : wave) * 32;   // the wave's first query position
+  const int qrow = qs + col;                  // this lane's query position
 
   const size_t qstride = (size_t)H * D;       // elements between consecutive tokens of q / o
   const size_t kstride = (size_t)a.Hkv * D;
@@ -163,8 +186,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   };
 
   int nkb = (S + kAttnBK - 1) / kAttnBK;
-  if (CAUSAL) nkb = min(nkb, (q0 + kAttnBQ - 1) / kAttnBK + 1);
-  const int wq_last = q0 + wave * 32 + 31;    // the wave's last query row
+  if (CAUSAL) nkb = min(nkb, (q0 + BQ - 1) / kAttnBK + 1);
 
   f32x16 acc_o[DT];
 #pragma unroll
@@ -216,44 +238,52 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
       dma_keys(ksn, jb + 1);
       dma_values(vtn, jb + 1);
     }
-    if (!CAUSAL || j0 <= wq_last) {
-      // scores S^T[key][query] for the block's 64 keys (two 32-key tiles, interleaved); the key
-      // fragments of step t+2 are read from LDS while the MFMAs of step t run
+    const int t0 = j0 + 32 * kh;            // the wave's first key of the block
+    // (tiles and waves' queries both start at multiples of 32, so every query of a wave sees at least the
+    // first key of a block that is not skipped)
+    if ((!SPLIT || t0 < S) && (!CAUSAL || t0 <= qs + 31)) {
+      // scores S^T[key][query] for the wave's keys of the block: two accumulators, one per 32-key tile
+      // (SPLIT: even and odd K16 steps), so that no MFMA waits for the one before; the key fragments of
+      // step t+2 are read from LDS while the MFMAs of step t run
       f32x16 sc[2] = {f32x16{}, f32x16{}};
-      bf16x8 kf[3][2];
-      kf[0][0] = rd_k(ksc, 0, 0);
-      kf[0][1] = rd_k(ksc, 0, 1);
-      kf[1][0] = rd_k(ksc, 1, 0);
-      kf[1][1] = rd_k(ksc, 1, 1);
+      bf16x8 kf[3][NT];
+#pragma unroll
+      for (int c = 0; c < NT; ++c) {
+        kf[0][c] = rd_k(ksc, 0, kh + c);
+        kf[1][c] = rd_k(ksc, 1, kh + c);
+      }
       // raised wave priority while a wave issues its MFMAs: the SIMD's other wave fills the
       // issue slots between them with its softmax VALU work
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int t = 0; t < KSTEPS; ++t) {
-        if (t + 2 < KSTEPS) {
-          kf[(t + 2) % 3][0] = rd_k(ksc, t + 2, 0);
-          kf[(t + 2) % 3][1] = rd_k(ksc, t + 2, 1);
+#pragma unroll
+        for (int c = 0; c < NT; ++c)
+          if (t + 2 < KSTEPS) kf[(t + 2) % 3][c] = rd_k(ksc, t + 2, kh + c);
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+          f32x16& d = sc[SPLIT ? t & 1 : c];
+          d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t % 3][c], qf[t], d, 0, 0, 0);
         }
-        sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t % 3][0], qf[t], sc[0], 0, 0, 0);
-        sc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t % 3][1], qf[t], sc[1], 0, 0, 0);
-        if (t + 2 < KSTEPS) QG_SG(kSchedDSRead, 2);
-        QG_SG(kSchedMFMA, 2);
+        if (t + 2 < KSTEPS) QG_SG(kSchedDSRead, NT);
+        QG_SG(kSchedMFMA, NT);
       }
       __builtin_amdgcn_s_setprio(0);
-      // key of register r in tile kt: kt*32 + (r/4)*8 + 4hh + r%4
-      const bool need_mask = (CAUSAL && j0 + kAttnBK - 1 > q0 + wave * 32) || j0 + kAttnBK > S;
+      if (SPLIT) sc[0] += sc[1];
+      // key of register r in tile kt: t0 + kt*32 + (r/4)*8 + 4hh + r%4
+      const bool need_mask = (CAUSAL && t0 + 32 * NT - 1 > qs) || t0 + 32 * NT > S;
       if (need_mask) {
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int kp = j0 + kt * 32 + (r >> 2) * 8 + 4 * hh + (r & 3);
+            const int kp = t0 + kt * 32 + (r >> 2) * 8 + 4 * hh + (r & 3);
             if (kp >= S || (CAUSAL && kp > qrow)) sc[kt][r] = -__builtin_inff();
           }
       }
       float mloc = -__builtin_inff();
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, sc[kt][r]);
       mloc = fmaxf(mloc, other_half(mloc));
@@ -272,33 +302,35 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
         m_run = m_new;
       }
       // p = exp2((s - m) * scale * log2 e), one fused multiply-add per score; P^T as packed bf16,
-      // per key tile: registers (2i, 2i+1). Tile 1's exponentials are written between the
-      // output-product MFMAs of tile 0 so the two overlap.
+      // per key tile: registers (2i, 2i+1). The second half's exponentials (SPLIT: of the tile's
+      // registers, else tile 1's) are written between the first output-product MFMAs so the two overlap.
       const float ms = m_run * sl2;
       float lsum = 0.0f;
-      uint32_t pf[2][8];
-      auto exp_tile = [&](int kt) {
+      uint32_t pf[NT][8];
+      auto exp_half = [&](int second) {
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
+        for (int i = 0; i < 8 * NT; i += 2) {
+          const int kt = SPLIT ? 0 : second;
+          const int r = SPLIT ? 8 * second + i : i;
           const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kt][r], sl2, -ms));
           const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[kt][r + 1], sl2, -ms));
           lsum += p0 + p1;
           pf[kt][r >> 1] = pack_bf16x2(p0, p1);
         }
       };
-      exp_tile(0);
-      // O^T += V^T P^T: K16 step u covers keys 16u..16u+15; lane half hh supplies the keys
+      exp_half(0);
+      // O^T += V^T P^T: K16 step u covers the wave's keys 16u..16u+15; lane half hh supplies the keys
       // 16u + 4hh + {0..3} and 16u + 8 + 4hh + {0..3} (its score registers 8(u%2)..8(u%2)+7).
       // The value fragments of step u+1 are read from LDS while the MFMAs of step u run.
       bf16x8 vf[2][DT];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) vf[0][dt] = rd_v(vtc, 0, dt);
+      for (int dt = 0; dt < DT; ++dt) vf[0][dt] = rd_v(vtc, 2 * kh, dt);
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (u + 1 < 4) {
+      for (int u = 0; u < 2 * NT; ++u) {
+        if (u + 1 < 2 * NT) {
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt) vf[(u + 1) & 1][dt] = rd_v(vtc, u + 1, dt);
+          for (int dt = 0; dt < DT; ++dt) vf[(u + 1) & 1][dt] = rd_v(vtc, 2 * kh + u + 1, dt);
         }
         const int kt = u >> 1;
         const int r0 = (u & 1) * 4;
@@ -306,7 +338,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
           acc_o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u & 1][dt], pb, acc_o[dt], 0, 0, 0);
-        if (u == 0) exp_tile(1);
+        if (u == 0) exp_half(1);
       }
       __builtin_amdgcn_s_setprio(0);
       l_run += lsum;
@@ -319,6 +351,40 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   for (int jb = 0; jb < nkb; jb += 2) {
     step(jb, ks0, vt0, ks1, vt1);
     if (jb + 1 < nkb) step(jb + 1, ks1, vt1, ks0, vt0);
+  }
+
+  if constexpr (SPLIT) {
+    // Merge the two waves of the same queries: the second half's output, maximum and sum go through the
+    // key and value buffers (the loop ends with a barrier), lane by lane. A wave that skipped every
+    // tile has maximum -inf and takes weight 0; the first half always holds key 0.
+    typedef __attribute__((address_space(3))) float lds_float;
+    lds_float* mo = (lds_float*)((wave & 1) ? (lds_char*)ks1 : (lds_char*)ks0);
+    lds_float* ml = (lds_float*)((wave & 1) ? (lds_char*)vt1 : (lds_char*)vt0);
+    if (kh == 1) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int a4 = 0; a4 < 4; ++a4)
+          *(__attribute__((address_space(3))) f32x4*)(mo + ((dt * 4 + a4) * 64 + lane) * 4) =
+              f32x4{acc_o[dt][4 * a4], acc_o[dt][4 * a4 + 1], acc_o[dt][4 * a4 + 2], acc_o[dt][4 * a4 + 3]};
+      ml[lane] = m_run;
+      ml[64 + lane] = l_run;
+    }
+    __syncthreads();
+    if (kh == 1) return;
+    const float m1 = ml[lane];
+    const float mm = fmaxf(m_run, m1);
+    const float w0 = __builtin_amdgcn_exp2f((m_run - mm) * sl2);
+    const float w1 = __builtin_amdgcn_exp2f((m1 - mm) * sl2);
+    l_run = l_run * w0 + ml[64 + lane] * w1;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int a4 = 0; a4 < 4; ++a4) {
+        const f32x4 o1 = *(const __attribute__((address_space(3))) f32x4*)(mo + ((dt * 4 + a4) * 64 + lane) * 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc_o[dt][4 * a4 + r] = acc_o[dt][4 * a4 + r] * w0 + o1[r] * w1;
+      }
   }
 
   // normalise and store: lane (col, hh) holds o[qrow][dt*32 + 8a + 4hh + {0..3}] in acc_o[dt][4a..4a+3]
@@ -338,9 +404,9 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
   }
 }
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool SPLIT>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_fwd_kernel(AttnArgs a) {
-  attn_body<D, CAUSAL>(a);
+  attn_body<D, CAUSAL, SPLIT>(a);
 }
 
 }  // namespace qg

@@ -304,7 +304,8 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a) {
       // p = exp2((s - m) * scale * log2 e), one fused multiply-add per score; P^T as packed bf16,
       // per key tile: registers (2i, 2i+1). The second half's exponentials (SPLIT: of the tile's
       // registers, else tile 1's) are written between the first output-product MFMAs so the two overlap.
-      const float ms = m_run * sl2;
+      // SPLIT: a half whose keys so far all score -inf (keys with infinities) keeps maximum -inf, weights 0
+      const float ms = (SPLIT && m_run == -__builtin_inff()) ? 0.0f : m_run * sl2;
       float lsum = 0.0f;
       uint32_t pf[NT][8];
       auto exp_half = [&](int second) {

@@ -22,3 +22,24 @@ def test_attention_forms(B, S, H, Hkv, D, causal):
                            seed=91, stream=(B, S, H, Hkv, D), q_std=4.0)
     check_full(torch, case)
     assert torch.equal(run(torch, case), run(torch, case))
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,S,H,Hkv,D", [(1, 40, 3, 3, 64), (1, 97, 3, 3, 128), (5, 129, 66, 11, 64), (9, 130, 36, 4, 128)])
+def test_attention_keys_scoring_minus_infinity(B, S, H, Hkv, D, causal):
+    """Keys 32..63 score -inf for every query (their first element is -inf, the queries' is positive): they
+    take no weight in either form, also where they are all that one of two waves has seen."""
+    import paper_2607_19438_amd as qg
+    torch = torch_or_skip()
+    gen = torch.Generator().manual_seed(7)
+    q, k, v = (torch.randn((B, S, h, D), generator=gen).to(torch.bfloat16) for h in (H, Hkv, Hkv))
+    q[..., 0] = q[..., 0].abs() + 0.5
+    k[:, 32:64, :, 0] = -float("inf")
+    o = qg.attention_prefill(q.cuda(), k.cuda(), v.cuda(), causal=causal)
+    kk, vv = (t.double().repeat_interleave(H // Hkv, dim=2) for t in (k, v))
+    s = torch.einsum("bqhd,bkhd->bhqk", q.double(), kk) / D ** 0.5
+    if causal:
+        s.masked_fill_(torch.ones(S, S, dtype=torch.bool).triu(1), -float("inf"))
+    ref = torch.einsum("bhqk,bkhd->bqhd", torch.softmax(s, dim=-1), vv)
+    # probabilities and outputs each rounded to bf16 (2^-9 relative), |sum p v| <= max |v|
+    assert (o.cpu().double() - ref).abs().max().item() <= 2 ** -8 * float(vv.abs().max())

@@ -165,6 +165,9 @@ __global__ __launch_bounds__(64 * kSmallWaves) void bucket_small_kernel(
     const int rank = __popcll(same & lt_mask);
     const int before = inrange ? mine[e] : 0;
     if (inrange && rank == 0) mine[e] = before + __popcll(same);
+    // the wave's next reads see this write (one wave's LDS accesses complete in order)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     e_of[i] = inrange ? e : -1;
     rank_of[i] = before + rank;
   }

@@ -119,13 +119,22 @@ int launch_small_jw(const qg::SmallArgs& a, int JW, long groups, hipStream_t s) 
   }
 }
 
-// M <= 16 (or up to 128 in MT blocks of 16 columns): 32 weight rows per workgroup; K is split
-// over workgroups only when there are fewer than 256 row blocks (or a wave would hold more than
-// kSmMaxJW chunks). With several column blocks the call is latency-bound rather than
-// weight-streaming, and a split keeps at least 4 chunks per workgroup (measured on the split
-// targets 32 / 64 / 128 / 256: 128x1024x1024 Q8 11.0 / 9.6 / 9.5 / 10.5 us, 128x2048x8192 Q8
-// 38 / 38 / 38 / 24 us, 96x2048x768 Q4 9.2 / 9.2 / 10.3 / 10.4 us; this rule picks the best of
-// each). Split partials go to the split-K workspace and a second kernel adds them in split order.
+// M <= 16 (or up to 128 in MT blocks of 16 columns): 32 weight rows per workgroup; K is split over
+// workgroups only when there are fewer than 256 row blocks (or a wave would hold more than kSmMaxJW
+// chunks) and K is longer than small_unsplit_k. Split partials go to the split-K workspace and a
+// second kernel adds them in split order: a dependent launch (about 2 us) and a partial per output and
+// workgroup, so a short K is faster in one workgroup's hands and a long one in few. One block: about
+// 1024 of K to a workgroup (two Q8 chunks or one Q4 chunk per wave); two blocks 512; more blocks at
+// least 4 chunks, as their matrix work per chunk is larger. Measured in captured graphs, splits filling
+// 256 workgroups (with several blocks: of 4 chunks at least) against this rule (us):
+//   1 row     Q4 2048x2048 5.7 -> 4.7, 6000x2048 6.6 -> 5.1, 512x8192 8.0 -> 6.4; Q8 1000x512 6.0 -> 2.9,
+//             512x2048 7.6 -> 5.0, 300x2560 9.1 -> 5.6, 1500x4128 7.7 -> 6.8
+//   16 rows   Q4 1024x1024 6.9 -> 3.8, 7168x2048 8.2 -> 6.4; Q8 4096x2048 7.1 -> 6.6, 768x6144 10.3 -> 7.6
+//   24 rows   Q4 1024x1024 6.0 -> 4.6, Q8 2048x512 5.5 -> 3.8, 256x2048 6.7 -> 5.9 (unsplit 7.2)
+//   64 rows   Q8 1024x512 6.3 -> 5.1; unsplit at K = 1024 256 columns 7.1 against 6.3, 2048 7.1 against 7.6
+//   128 rows  Q8 1024x512 8.3 -> 7.2; unsplit at K = 1024 11.0 against 9.4
+constexpr int small_unsplit_k(int MT) { return MT == 1 ? 2048 : MT == 2 ? 1024 : 512; }
+
 template <int FMT>
 int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStream_t s) {
   using F = qg::SmallFmt<FMT>;
@@ -133,7 +142,9 @@ int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStr
   const long nc = (t.K + F::kKC - 1) / F::kKC;
   const long P = (t.N + qg::kSmRows - 1) / qg::kSmRows;
   long S = std::min<long>(nc, (kSmTargetGroups + P - 1) / P);
-  if (MT > 1) S = std::min<long>(S, std::max<long>(1, nc / 4));
+  if (t.K <= small_unsplit_k(MT)) S = 1;
+  else if (MT == 1) S = std::min<long>(S, (t.K + 1023) / 1024);
+  else S = std::min<long>(S, MT == 2 ? std::min<long>(nc / 4, (t.K + 511) / 512) : std::max<long>(1, nc / 4));
   S = std::max<long>(S, (nc + qg::kSmWaves * kSmMaxJW - 1) / (qg::kSmWaves * kSmMaxJW));
   const long cps = (nc + S - 1) / S;
   S = (nc + cps - 1) / cps;

@@ -52,6 +52,18 @@ def test_small_m_shapes(fmt, M, N, K):
     check(case, run(torch, case).cpu().numpy())
 
 
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("M,K", [(M, K) for M in (1, 16) for K in (2016, 2048, 2080, 3072, 3104, 4128)] +
+                         [(M, K) for M in (17, 32) for K in (992, 1024, 1056, 2080)] +
+                         [(M, K) for M in (33, 128) for K in (480, 512, 544, 1056)])
+def test_small_m_split_rule_edges(M, K, fmt):
+    """Around the longest K that one workgroup takes (2048, 1024 and 512 for one, two and more blocks of 16
+    rows) and around changes of the number of splits, with ragged N."""
+    torch = torch_or_skip()
+    case = synth.dense_case(f"small_edge_{synth.FMT_NAMES[fmt]}_{M}x75x{K}", fmt, M, 75, K, seed=12, stream=(M, 75, K))
+    check(case, run(torch, case).cpu().numpy())
+
+
 @pytest.mark.parametrize("M", [1, 4, 16])
 @pytest.mark.parametrize("fmt,N,K", [(synth.FMT_Q4, 8192, 3072), (synth.FMT_Q8, 8192, 2048),
                                      (synth.FMT_Q8, 2048, 8192), (synth.FMT_Q4, 1536, 2048),

@@ -292,7 +292,9 @@ __device__ __forceinline__ void dir_body(const TileArgs& a, const DirItem& it, i
   issue_x(0, x0);
   wait_vmcnt_lgkm0<0>();
   // Each stage is entered through a barrier once its activation DMA has landed; only the NW + 1
-  // (or more) weight and scale loads issued after that DMA may still be in flight.
+  // (or more) weight and scale loads issued after that DMA may still be in flight. The general form's last
+  // stage uses its weights behind run-time breaks, where their loads could be sunk to, so that fewer
+  // follow the DMA than the count allows for: it is entered with nothing in flight.
   int st = 0;
   auto pair = [&](auto last) {       // stages st (of x0) and st + 1 (of x1)
     __builtin_amdgcn_s_barrier();
@@ -300,7 +302,7 @@ __device__ __forceinline__ void dir_body(const TileArgs& a, const DirItem& it, i
     __builtin_amdgcn_sched_barrier(0);
     issue(st + 1, w[1], s[1]);
     step(std::true_type{}, st, x0, w[0], s[0]);
-    wait_vmcnt_lgkm0<NW + 1>();
+    wait_vmcnt_lgkm0<!FAST && decltype(last)::value ? 0 : NW + 1>();
     __builtin_amdgcn_s_barrier();
     if constexpr (decltype(last)::value) {
       step(std::false_type{}, st + 1, x1, w[1], s[1]);
@@ -316,6 +318,7 @@ __device__ __forceinline__ void dir_body(const TileArgs& a, const DirItem& it, i
   if (st + 2 == nst) {
     pair(std::true_type{});
   } else {
+    if constexpr (!FAST) wait_vmcnt_lgkm0<0>();
     __builtin_amdgcn_s_barrier();
     step(std::false_type{}, st, x0, w[0], s[0]);
   }

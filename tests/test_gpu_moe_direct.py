@@ -21,7 +21,11 @@ EXPERTS = [10, 13, 24, 70, 200]
 
 
 @pytest.mark.parametrize("fmt", [synth.FMT_Q8, synth.FMT_Q4])
-@pytest.mark.parametrize("inter,K,misaligned", [(18, 32, False), (16, 96, False), (17, 256, False), (40, 544, False),
+# K that is not whole stages ends on an odd or an even number of them: stages of four 64-wide steps (32- and
+# 64-row groups) 32, 96, 160 one, 288, 416, 480 two, 544 three; of two (128-row groups) 32, 96 one, 160 two,
+# 288 three, 416, 480 four, 544 five
+@pytest.mark.parametrize("inter,K,misaligned", [(18, 32, False), (16, 96, False), (20, 160, False), (17, 256, False),
+                                                (33, 288, False), (24, 416, False), (40, 480, False), (40, 544, False),
                                                 (72, 768, False), (72, 768, True), (64, 2048, False)])
 def test_direct_forms_bitwise(fmt, inter, K, misaligned):
     torch = torch_or_skip()

@@ -463,7 +463,9 @@ int qgemm_moe_bucket(const int32_t* token_expert_idx, const int32_t* expert_offs
   if (!ws) return fail(QGEMM_EHIP, "hipGetDevice failed");
   int chunk, nblk;
   bucket_geometry(n_assign, &chunk, &nblk);
-  int rc = bucket_small(n_assign, E) ? QGEMM_OK : grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
+  // also where one workgroup needs no counts: a later, larger call may be inside a capture, where the
+  // workspace cannot be allocated
+  int rc = grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
   if (rc != QGEMM_OK) return rc;
   size_t one = 0;
   if (ws->flag == nullptr) {
@@ -543,7 +545,7 @@ int qgemm_moe(const void* x, const int32_t* token_expert_idx, const int32_t* exp
     int chunk, nblk;
     bucket_geometry(n, &chunk, &nblk);
     rc = grow(&ws->perm, &ws->perm_cap, (size_t)n);
-    if (rc == QGEMM_OK && !bucket_small(n, E)) rc = grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
+    if (rc == QGEMM_OK) rc = grow(&ws->counts, &ws->counts_cap, (size_t)nblk * E);
     if (rc == QGEMM_OK && ws->flag == nullptr) {
       size_t one = 0;
       rc = grow(&ws->flag, &one, 1);

@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqgemm.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("qgemm_api.hip", "moe_direct.hip")]
 DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("qgemm_kernels.hpp", "qgemm_aux.hpp", "qgemm_smallm.hpp", "moe_direct.hpp",
-                                                  "moe_direct_api.hpp", "attn_kernels.hpp")] + [
+                                                  "moe_direct_api.hpp", "tile_rules.hpp", "attn_kernels.hpp")] + [
     os.path.join(os.path.dirname(HERE), "include", "qgemm.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

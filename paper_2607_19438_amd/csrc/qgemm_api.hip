@@ -16,6 +16,7 @@
 #include "qgemm_kernels.hpp"
 #include "qgemm_aux.hpp"
 #include "qgemm_smallm.hpp"
+#include "tile_rules.hpp"
 #include "moe_direct_api.hpp"
 #include "attn_kernels.hpp"
 
@@ -96,8 +97,6 @@ int split_workspace(size_t floats, float** out) {
   *out = w.first;
   return QGEMM_OK;
 }
-
-constexpr int kMinStepsPerSplit = 12;
 
 constexpr long kSmTargetGroups = 256;   // workgroups (of eight waves) to fill the CUs without a K split
 constexpr int kSmMaxJW = 8;             // chunks per wave held in registers
@@ -218,30 +217,12 @@ int dense_dispatch(qg::TileArgs a, const void* wq, const void* sc, hipStream_t s
     if ((long)((a.N + 127) / 128) * MT <= 512) return small_dispatch<FMT>(a, wq, sc, s);
   }
   a.splits = 1;
-  const long big = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
-  if (a.M >= 256 && a.N >= 256 && big >= 200) return launch_dense<FMT, 256, 256, 2, 4, 2>(a, wq, sc, s);
-  const int nk = (a.K + 63) / 64;
-  // up to 1024 rows with few 256x256 tiles: eight-wave tiles of half that size, twice the tiles, so
-  // half the K split and half the fp32 partials; the split keeps tiles x splits <= 256 (one round).
-  // Up to 2048 rows only where these tiles need no split. From 256 rows on 256x128 (each weight is
-  // dequantised for 256 rows, not 128), below 128x256. Measured, 128x256 against 256x128: Q4
-  // 512x8192x3072 45.6 vs 40.1 us, 1024x4096x4096 50.9 vs 47.7, 768x1536x2048 25.5 vs 22.6,
-  // 1536x4096x4096 67.4 vs 60.4; Q8 512x2048x2048 24.0 vs 23.4, 2048x4096x2048 43.6 vs 41.4,
-  // 300x5000x4096 32.1 vs 28.7; and 256x128 against 256x256: Q8 2048x2048x8192 84.2 vs 83.9 (two
-  // splits against four), 2048x8192x2048 81 vs 69.7.
-  const bool tall = a.M >= 256;
-  const long t2 = tall ? (long)((a.M + 255) / 256) * ((a.N + 127) / 128) : (long)((a.M + 127) / 128) * ((a.N + 255) / 256);
-  if (a.M >= 128 && a.N >= 256 && ((long)a.M * a.N) % 4 == 0 && (a.M <= 1024 || (a.M <= 2048 && t2 > 128))) {
-    int S = (int)std::max<long>(1, std::min<long>(8, 256 / t2));
-    while (S > 1 && nk / S < kMinStepsPerSplit) --S;
-    return tall ? launch_split<FMT, 256, 128>(a, S, wq, sc, s) : launch_split<FMT, 128, 256>(a, S, wq, sc, s);
-  }
-  // few 256x256 tiles but a long K: split K over several workgroups per tile so that every CU gets
-  // a 256x256 tile
-  if (a.M >= 256 && a.N >= 256 && ((long)a.M * a.N) % 4 == 0) {
-    int S = (int)std::min<long>(8, (256 + big - 1) / big);
-    while (S > 1 && nk / S < kMinStepsPerSplit) --S;
-    if (S > 1) return launch_split<FMT, 256, 256>(a, S, wq, sc, s);
+  const qg::DensePlan plan = qg::dense_plan(FMT == qg::kQ4, a.M, a.N, a.K);
+  switch (plan.tile) {
+    case qg::DenseTile::k256x256: return launch_split<FMT, 256, 256>(a, plan.splits, wq, sc, s);
+    case qg::DenseTile::k256x128: return launch_split<FMT, 256, 128>(a, plan.splits, wq, sc, s);
+    case qg::DenseTile::k128x256: return launch_split<FMT, 128, 256>(a, plan.splits, wq, sc, s);
+    case qg::DenseTile::k128x128: break;
   }
   return launch_dense<FMT, 128, 128, 2, 2, 2>(a, wq, sc, s);
 }

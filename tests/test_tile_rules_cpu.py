@@ -1,0 +1,99 @@
+"""Host-side checks of the rules that pick a tile from a call's sizes (``tile_rules.hpp``), compiled by
+itself with the host compiler. No test here touches a GPU.
+
+Dense, 256 to 2048 rows: the half-size tile is 256x128 or 128x256, whichever needs fewer rounds of one
+workgroup per CU and fewer K steps, so that a call does not pay a second round, or chains of K twice as long,
+for the tile's shape alone.
+"""
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2607_19438_amd import build
+
+MAIN = """
+#include <cstdio>
+#include "tile_rules.hpp"
+int main() {
+  long q4, M, N, K;
+  while (std::scanf("%ld %ld %ld %ld", &q4, &M, &N, &K) == 4) {
+    const qg::DensePlan p = qg::dense_plan(q4 != 0, M, N, K);
+    std::printf("%d %d\\n", (int)p.tile, p.splits);
+  }
+}
+"""
+TILES = [(256, 256), (256, 128), (128, 256), (128, 128)]     # in the order of the enumeration
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "main.cpp").write_text(MAIN)
+    exe = str(d / "rules")
+    subprocess.run(["g++", "-std=c++20", "-Wall", "-Werror", "-I", build.CSRC, str(d / "main.cpp"), "-o", exe], check=True)
+
+    def run(calls):
+        text = "".join(f"{int(q4)} {M} {N} {K}\n" for q4, M, N, K in calls)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split()
+        return [(TILES[int(out[i])], int(out[i + 1])) for i in range(0, len(out), 2)]
+    return run
+
+
+def cd(a, b):
+    return -(-a // b)
+
+
+def rounds_steps(tile, splits, M, N, K):
+    items = cd(M, tile[0]) * cd(N, tile[1]) * splits
+    return cd(items, 256), cd(cd(K, 64), splits)
+
+
+@pytest.mark.parametrize("M,N,K", [(1100, 7168, 2048), (1904, 4285, 3040), (1028, 6912, 2048), (640, 11008, 4096),
+                                   (785, 8448, 1984), (803, 8232, 8064)])
+def test_dense_takes_one_round_where_a_half_size_tile_has_it(plans, M, N, K):
+    for q4 in (False, True):
+        ((tile, splits),) = plans([(q4, M, N, K)])
+        assert tile == (128, 256) and rounds_steps(tile, splits, M, N, K)[0] == 1
+
+
+@pytest.mark.parametrize("q4,M,N,K,tile,splits", [
+    (True, 600, 4096, 4096, (128, 256), 3), (True, 576, 6340, 3360, (128, 256), 2),
+    (False, 590, 5760, 7200, (128, 256), 2), (True, 590, 5760, 7200, (128, 256), 2),
+    (False, 600, 4096, 4096, (256, 128), 2),                 # Q8: a 256x128 step is so much cheaper
+    (True, 512, 8192, 3072, (256, 128), 2), (True, 1024, 4096, 4096, (256, 128), 2), (True, 768, 1536, 2048, (256, 128), 2),
+    (True, 1536, 4096, 4096, (256, 128), 1), (False, 512, 2048, 2048, (256, 128), 2), (False, 2048, 4096, 2048, (256, 128), 1),
+    (False, 300, 5000, 4096, (256, 128), 3), (False, 2048, 2048, 8192, (256, 256), 4), (False, 2048, 8192, 2048, (256, 256), 1),
+    (False, 1506, 2688, 7616, (256, 128), 2), (True, 1154, 3088, 576, (128, 128), 1),
+    (False, 200, 1000, 4128, (128, 256), 5), (False, 255, 257, 288, (128, 128), 1)])
+def test_dense_measured_calls(plans, q4, M, N, K, tile, splits):
+    assert plans([(q4, M, N, K)]) == [(tile, splits)]
+
+
+def test_dense_half_size_tiles_never_add_a_round(plans):
+    """Against the same call on the other half-size tile with the splits that it would get: no more rounds,
+    and within one round no more than 1.5 times the K steps plus a split's cost."""
+    rng = random.Random(5)
+    calls = []
+    while len(calls) < 4000:
+        M, N, K = int(256 * 8 ** rng.random()), int(256 * 64 ** rng.random()), 32 * int(16 * 16 ** rng.random())
+        if M * N % 4 == 0:
+            calls.append((rng.random() < 0.5, M, N, K))
+    seen = set()
+    for (q4, M, N, K), (tile, splits) in zip(calls, plans(calls)):
+        assert 1 <= splits <= 8 and (splits == 1 or cd(K, 64) // splits >= 12)
+        if tile not in ((256, 128), (128, 256)):
+            continue
+        seen.add(tile)
+        other = tile[::-1]
+        S = max(1, min(8, 256 // (cd(M, other[0]) * cd(N, other[1]))))
+        while S > 1 and cd(K, 64) // S < 12:
+            S -= 1
+        r, s = rounds_steps(tile, splits, M, N, K)
+        r2, s2 = rounds_steps(other, S, M, N, K)
+        sums = 6 + S * M * N / 2 ** 20 if S > 1 else 0
+        assert r <= r2, (q4, M, N, K)
+        if r == 1 and tile == (256, 128):
+            assert s <= 1.5 * s2 + sums, (q4, M, N, K)
+    assert seen == {(256, 128), (128, 256)}

@@ -67,7 +67,7 @@ int check_common(int N, int K, int fmt) {
 template <int FMT, int BM, int BN, int WM, int WN, int XS>
 int launch_dense(const qg::TileArgs& a, const void* wq, const void* sc, hipStream_t s) {
   const long tiles = (long)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * a.splits;
-  if (tiles > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "too many tiles");
+  if (!qg::grid_fits(tiles, WM * WN * 64)) return fail(QGEMM_EUNSUPPORTED, "too many tiles");
   hipLaunchKernelGGL((qg::dense_kernel<FMT, BM, BN, WM, WN, XS>), dim3((unsigned)tiles), dim3(WM * WN * 64), 0, s, a,
                      static_cast<const uint8_t*>(wq), static_cast<const uint16_t*>(sc));
   return check_launch("qgemm_dense");
@@ -147,7 +147,7 @@ int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStr
   S = std::max<long>(S, (nc + qg::kSmWaves * kSmMaxJW - 1) / (qg::kSmWaves * kSmMaxJW));
   const long cps = (nc + S - 1) / S;
   S = (nc + cps - 1) / cps;
-  if (P * S > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "too many workgroups");
+  if (!qg::grid_fits(P * S, qg::kSmWaves * 64)) return fail(QGEMM_EUNSUPPORTED, "too many workgroups");
   int JW = 1;
   while (JW * qg::kSmWaves < cps) JW *= 2;
   int nbp_log2 = 0;
@@ -244,7 +244,7 @@ int launch_moe_cfg(qg::TileArgs a, const void* const* wq, const void* const* sc,
     const long mt_bound = (long)(a.M + BM - 1) / BM + ne;
     constexpr long kDeal = 8L * qg::kMoeRun;   // groups per round over the 8 XCDs
     const long grid = (mt_bound + kDeal - 1) / kDeal * kDeal * nt;
-    if (grid > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "too many tiles");
+    if (!qg::grid_fits(grid, WM * WN * 64)) return fail(QGEMM_EUNSUPPORTED, "too many tiles");
     hipLaunchKernelGGL((qg::moe_kernel<FMT, BM, BN, WM, WN, XS, SWI, CMB>), dim3((unsigned)grid), dim3(WM * WN * 64), 0,
                        s, a, ep);
     const int rc = check_launch("qgemm_moe");
@@ -257,7 +257,7 @@ int launch_moe_cfg(qg::TileArgs a, const void* const* wq, const void* const* sc,
 // (token, column tile)).
 inline int moe_tile_bn(long M, int E) { return (M / E) <= 32 ? 128 : 256; }
 
-// Few rows per expert go to the direct kernel (moe_direct.hip, where that rule stands); above that,
+// Few rows per expert go to the direct kernel (tile_rules.hpp, where that rule stands); above that,
 // from the mean rows per expert (the host does not see the routing), about 100-200 rows fit one
 // 192-row tile each and larger groups use 256-row tiles. The fused combine needs a workgroup that
 // stores whole column tiles of its rows: it keeps 128x128 four-wave tiles for short prompts (T=128
@@ -267,8 +267,8 @@ int launch_moe(qg::TileArgs a, const void* const* wq, const void* const* sc, int
   const long mean_rows = (long)a.M / E;
   if constexpr (CMB) {
     if (mean_rows <= 32) return launch_moe_cfg<FMT, 128, 128, 2, 2, 2, false, true>(a, wq, sc, E, s);
-  } else if (qg::moe_direct_takes(FMT, a.M, E)) {
-    if (!qg::moe_direct_launch(FMT, SWI, a, wq, sc, E, s)) return fail(QGEMM_EUNSUPPORTED, "too many tiles");
+  } else if (const int rows = qg::moe_direct_rows(FMT == qg::kQ4, SWI, a.M, E, SWI ? a.swi_inter : a.N)) {
+    qg::moe_direct_launch(rows, FMT, SWI, a, wq, sc, E, s);
     return check_launch("qgemm_moe");
   }
   if (mean_rows > 192) return launch_moe_cfg<FMT, 256, 256, 2, 4, 2, SWI, CMB>(a, wq, sc, E, s);
@@ -685,7 +685,7 @@ int qgemm_swiglu(const float* y1, void* h, int rows, int inter, hipStream_t stre
   if (!aligned16(y1) || !aligned16(h)) return fail(QGEMM_EALIGN, "y1 and h must be 16-byte aligned");
   const long groups = (long)rows * (inter / 8);
   const long blocks = (groups + 255) / 256;
-  if (blocks > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "problem too large");
+  if (!qg::grid_fits(blocks, 256)) return fail(QGEMM_EUNSUPPORTED, "problem too large");
   (void)hipGetLastError();
   hipLaunchKernelGGL(qg::swiglu_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, y1,
                      static_cast<uint16_t*>(h), groups, inter);
@@ -703,7 +703,7 @@ int qgemm_moe_combine(const float* y2, const float* route_w, float* out, int T, 
   const int v = (N % 8 == 0) ? 8 : 4;
   const long groups = (long)T * (N / v);
   const long blocks = (groups + 255) / 256;
-  if (blocks > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "problem too large");
+  if (!qg::grid_fits(blocks, 256)) return fail(QGEMM_EUNSUPPORTED, "problem too large");
   (void)hipGetLastError();
   // column mapping by where y2 will come from: a y2 that fits well inside the 256 MB last-level
   // cache (just written by the down projection) reads faster with wave-contiguous 16-byte
@@ -743,7 +743,7 @@ int qgemm_attention_prefill(const void* q, const void* k, const void* v, void* o
   const bool split = work128 <= (!causal ? 256 : D == 64 ? 640 : 400);
   const int bq = split ? qg::kAttnBQ<true> : qg::kAttnBQ<false>;
   const long nqb = (S + bq - 1) / bq;
-  if ((long)B * H * nqb > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "too many workgroups");
+  if (!qg::grid_fits((long)B * H * nqb, qg::kAttnThreads)) return fail(QGEMM_EUNSUPPORTED, "too many workgroups");
   if (B == 0 || S == 0) return ok();
   if (!q || !k || !v || !o) return fail(QGEMM_EINVAL, "null pointer argument");
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o))

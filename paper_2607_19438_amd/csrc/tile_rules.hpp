@@ -17,6 +17,10 @@ constexpr int kMinStepsPerSplit = 12;
 
 inline long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
+// Whether a launch can have so many workgroups. The runtime counts a grid's threads in 32 bits and does not
+// refuse more: a launch of 2^24 + 1484 workgroups of 256 threads returned success and ran 1484 of them.
+inline bool grid_fits(long workgroups, int threads) { return workgroups <= 0xffffffffL / threads; }
+
 // Splits of nk K steps, at most `most` (and eight), each of at least kMinStepsPerSplit steps.
 inline int k_splits(long most, long nk) {
   int S = (int)std::max<long>(1, std::min<long>(8, most));
@@ -73,6 +77,47 @@ inline DensePlan dense_plan(bool q4, long M, long N, long K) {
     if (S > 1) return {DenseTile::k256x256, S};
   }
   return {DenseTile::k128x128, 1};
+}
+
+// The direct MoE kernel (moe_direct.hpp): one 32-row block of weights per wave, `waves` of them and so
+// 32 x waves columns per workgroup (fused gate/up 16 x waves of h).
+constexpr int kMoeSlice = 128;   // experts per launch
+
+inline int moe_direct_waves(int rows) { return rows == 64 ? 8 : 4; }
+
+inline long moe_direct_tiles(int rows, bool swi, long cols) {
+  return ceil_div(cols, (swi ? 16 : 32) * moe_direct_waves(rows));
+}
+
+// Upper bound of sum_e ceil(c_e / rows): every active expert (at most one per row) adds one group and its
+// further rows whole groups.
+inline long moe_direct_groups(int rows, long M, long experts) {
+  const long active = std::min(experts, M);
+  return (M - active) / rows + active;
+}
+
+// Rows per group of the direct kernel for M rows over E experts and cols output columns, 0 where the staged
+// tiles take the call. From the mean rows per expert (the host does not see the routing).
+// Taller groups dequantise a large expert's weights fewer times, shorter ones leave more workgroups
+// and registers for loads in flight; four waves per workgroup spread few items over more CUs.
+// Measured on E=128 top-8 hidden 2048 inter 768 Q4 (gate/up + SiLU, down; us), against the staged
+// tiles that took these calls before (64x128 / 128x128 up to 32 rows, 192x256 above):
+//   T=4    32-row 19.6, 9.8     64-row 20.8, 10.4    staged 27.5, 17.0
+//   T=128  32-row 66.9, 34.2    64-row 67.9, 35.4    128-row 77.5, 42.6   staged 96.0, 57.4
+//   T=500  32-row 94.6, 54.7    64-row 86.3, 50.5    128-row 93.7, 59.4   staged 114, 75.4
+//   T=1024 64-row 119, 73.5     128-row 114, 77.4    staged 124, 81.6
+//   T=1536 64-row 149, 93.2     128-row 135, 96.4    staged 137, 95.1
+// and E=64 top-6 hidden 2048 inter 1056 Q8 (its 64-row form spills; 32-row up to a mean of 32):
+//   T=300 (mean 28)   32-row 83.8, 51.6   128-row 87.5, 48.5   staged 105, 57.2
+//   T=777 (mean 73)   32-row 166, 88.6    128-row 106, 65.4    staged 160, 78.7
+//   T=1200 (mean 112) 128-row 127, 90.6   staged 167, 86.1
+inline int moe_direct_rows(bool q4, bool swi, long M, long E, long cols) {
+  const long mean = M / E;
+  if (mean > (q4 ? 80 : 96)) return 0;
+  const int rows = mean <= (q4 ? 16 : 32) ? 32 : q4 && mean <= 48 ? 64 : 128;
+  // the staged tiles are larger, and so their grids smaller
+  const long items = moe_direct_groups(rows, M, std::min<long>(E, kMoeSlice)) * moe_direct_tiles(rows, swi, cols);
+  return grid_fits(items, 64 * moe_direct_waves(rows)) ? rows : 0;
 }
 
 }  // namespace qg

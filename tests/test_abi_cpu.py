@@ -98,6 +98,15 @@ def test_moe_host_validation(qmod):
     assert lib.qgemm_swiglu(16, 16, 0, 16, None) == 0
     assert lib.qgemm_moe_combine(16, 16, 16, 4, 2, 6, None) == -1
     assert lib.qgemm_moe_combine(16, 16, 16, 0, 2, 8, None) == 0
+    # one expert with 200 rows on staged tiles: 8 groups x 2^20 column tiles of 512 threads, 2^32 threads
+    one = (ctypes.c_void_p * 1)(16)
+    assert lib.qgemm_moe_grouped(16, 16, 16, one, one, 16, 200, 1, 1, 1 << 28, 32, 0, None) == -3
+    assert "too many tiles" in qmod.last_error()
+    # 128 experts of one row: 2^24 + 128 workgroups of the direct kernel, more threads than a launch counts,
+    # and still too many as staged tiles
+    many = (ctypes.c_void_p * 128)(*[16] * 128)
+    assert lib.qgemm_moe_gate_up_swiglu(16, 16, 16, many, many, 16, 128, 128, 1, (1 << 23) + 64, 32, 1, None) == -3
+    assert "too many tiles" in qmod.last_error()
     # fused down projection + combine: h, perm, offsets, wq, scales, route_w, y2, out, T, E, topk, N, K, fmt
     dc = lib.qgemm_moe_down_combine
     assert dc(16, 16, 16, ptrs, ptrs, 16, 16, 16, 4, 4, 2, 130, 64, 0, None) == -1       # N % 4
@@ -123,6 +132,7 @@ def test_attention_host_validation(qmod):
     assert f(16, 16, 16, 16, 1, 8, 4, 4, 128, float("nan"), 1, None) == -1
     assert f(16, 16, 16, 16, -1, 8, 4, 4, 128, 0.1, 1, None) == -1   # B < 0
     assert f(16, 16, 16, 16, 1, 1 << 20, 32, 4, 128, 0.1, 1, None) == -3   # S*H*D >= 2^31
+    assert f(16, 16, 16, 16, 1 << 20, 1, 16, 4, 64, 0.1, 1, None) == -3   # 2^24 workgroups, 2^32 threads
     assert f(16, 16, 16, 16, 0, 8, 4, 4, 128, 0.1, 1, None) == 0     # empty batch: no-op
     assert f(16, 16, 16, 16, 1, 0, 4, 4, 128, 0.1, 1, None) == 0     # empty prompt: no-op
     assert f(None, 16, 16, 16, 1, 8, 4, 4, 128, 0.1, 1, None) == -1  # null pointer

@@ -17,10 +17,16 @@ MAIN = """
 #include <cstdio>
 #include "tile_rules.hpp"
 int main() {
-  long q4, M, N, K;
-  while (std::scanf("%ld %ld %ld %ld", &q4, &M, &N, &K) == 4) {
-    const qg::DensePlan p = qg::dense_plan(q4 != 0, M, N, K);
-    std::printf("%d %d\\n", (int)p.tile, p.splits);
+  char what;
+  long q4, a, b, c, d;
+  while (std::scanf(" %c %ld %ld %ld %ld %ld", &what, &q4, &a, &b, &c, &d) == 6) {
+    if (what == 'd') {
+      const qg::DensePlan p = qg::dense_plan(q4 != 0, a, b, c);
+      std::printf("%d %d\\n", (int)p.tile, p.splits);
+    } else {
+      const int rows = qg::moe_direct_rows(q4 != 0, d != 0, a, b, c);
+      std::printf("%d %ld\\n", rows, rows ? qg::moe_direct_groups(rows, a, b) * qg::moe_direct_tiles(rows, d != 0, c) : 0);
+    }
   }
 }
 """
@@ -28,17 +34,28 @@ TILES = [(256, 256), (256, 128), (128, 256), (128, 128)]     # in the order of t
 
 
 @pytest.fixture(scope="module")
-def plans(tmp_path_factory):
+def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("rules")
     (d / "main.cpp").write_text(MAIN)
     exe = str(d / "rules")
     subprocess.run(["g++", "-std=c++20", "-Wall", "-Werror", "-I", build.CSRC, str(d / "main.cpp"), "-o", exe], check=True)
 
-    def run(calls):
-        text = "".join(f"{int(q4)} {M} {N} {K}\n" for q4, M, N, K in calls)
+    def run(what, calls):
+        text = "".join(" ".join([what, *(str(int(v)) for v in c), *["0"] * (5 - len(c))]) + "\n" for c in calls)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split()
-        return [(TILES[int(out[i])], int(out[i + 1])) for i in range(0, len(out), 2)]
+        return [(int(out[i]), int(out[i + 1])) for i in range(0, len(out), 2)]
     return run
+
+
+@pytest.fixture(scope="module")
+def plans(rules):
+    return lambda calls: [(TILES[t], s) for t, s in rules("d", calls)]
+
+
+@pytest.fixture(scope="module")
+def direct(rules):
+    """(rows per group, workgroups of one launch) of calls (q4, rows, experts, columns, fused gate/up)."""
+    return lambda calls: rules("m", calls)
 
 
 def cd(a, b):
@@ -97,3 +114,12 @@ def test_dense_half_size_tiles_never_add_a_round(plans):
         if r == 1 and tile == (256, 128):
             assert s <= 1.5 * s2 + sums, (q4, M, N, K)
     assert seen == {(256, 128), (128, 256)}
+
+
+@pytest.mark.parametrize("q4,M,E,cols,swi", [(True, 65536, 4096, 494400, True), (True, 128, 128, (1 << 23) + 64, True),
+                                             (False, 128, 128, (1 << 24) + 128, False), (True, 4096, 128, 1 << 24, False)])
+def test_direct_grid_of_2_to_the_32_threads_is_left_to_the_staged_tiles(direct, q4, M, E, cols, swi):
+    """The runtime counts a grid's threads in 32 bits: more of them wrap, and part of the output stays unwritten."""
+    assert direct([(q4, M, E, cols, swi)])[0][0] == 0
+    (rows, groups), = direct([(q4, M, E, cols // 8, swi)])
+    assert rows > 0 and 0 < groups * 64 * (8 if rows == 64 else 4) < 1 << 32

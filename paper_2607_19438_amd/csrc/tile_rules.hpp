@@ -99,25 +99,47 @@ inline long moe_direct_groups(int rows, long M, long experts) {
 // Rows per group of the direct kernel for M rows over E experts and cols output columns, 0 where the staged
 // tiles take the call. From the mean rows per expert (the host does not see the routing).
 // Taller groups dequantise a large expert's weights fewer times, shorter ones leave more workgroups
-// and registers for loads in flight; four waves per workgroup spread few items over more CUs.
-// Measured on E=128 top-8 hidden 2048 inter 768 Q4 (gate/up + SiLU, down; us), against the staged
-// tiles that took these calls before (64x128 / 128x128 up to 32 rows, 192x256 above):
-//   T=4    32-row 19.6, 9.8     64-row 20.8, 10.4    staged 27.5, 17.0
-//   T=128  32-row 66.9, 34.2    64-row 67.9, 35.4    128-row 77.5, 42.6   staged 96.0, 57.4
-//   T=500  32-row 94.6, 54.7    64-row 86.3, 50.5    128-row 93.7, 59.4   staged 114, 75.4
-//   T=1024 64-row 119, 73.5     128-row 114, 77.4    staged 124, 81.6
-//   T=1536 64-row 149, 93.2     128-row 135, 96.4    staged 137, 95.1
-// and E=64 top-6 hidden 2048 inter 1056 Q8 (its 64-row form spills; 32-row up to a mean of 32):
-//   T=300 (mean 28)   32-row 83.8, 51.6   128-row 87.5, 48.5   staged 105, 57.2
-//   T=777 (mean 73)   32-row 166, 88.6    128-row 106, 65.4    staged 160, 78.7
-//   T=1200 (mean 112) 128-row 127, 90.6   staged 167, 86.1
+// and registers for loads in flight; four waves per workgroup spread few items over more CUs. So 32 rows
+// while the mean is small, and further while the next height would leave the chip idle: Q4, one 64-row
+// workgroup (eight waves) per CU, above a mean of 32, where an expert takes two 32-row groups, one per two CUs;
+// Q8, three 128-row workgroups per two CUs. Over 200 random calls whose height these limits moved (8 to 128
+// experts, 17 to 80 rows on average, random logits with or without a Zipf bias; gate/up and down together)
+// the Q4 ones take 0.74 of the time that they take with limits on the mean alone (16, 48; the slowest 1.04),
+// the Q8 ones 0.94 (32; 1.07).
+// Measured (gate/up + SiLU, down; us) on routing by random logits, against the staged tiles that took these
+// calls before (64x128 / 128x128 up to a mean of 32 rows, 192x256 above; * the one taken):
+//   Q4 E=128 top-8 2048/768   T=128  32-row 65.2, 29.4*  64-row 60.2, 31.4   128-row 73.6, 38.6   staged 92.9, 54.5
+//                             T=512  32-row 85.8, 44.6   64-row 77.3, 42.1*  128-row 88.1, 50.1   staged 99.5, 64.7
+//                             T=1024 32-row 133, 82.7    64-row 115, 70.9    128-row 112, 72.3*   staged 122, 79.7
+//   Q4 E=256 top-8 4096/2048  T=512  32-row 629, 353     64-row 630, 345*   128-row 737, 397     staged 870, 570
+//     the same with a Zipf bias      32-row 389, 221     64-row 345, 194*   128-row 355, 201     staged 456, 259
+//   Q4 E=8 top-2 4096/2048    T=128  32-row 35.6, 21.3*  64-row 46.2, 26.9   128-row 39.9, 23.2   staged 42.8, 29.8
+//   Q8 E=64 top-6 2048/1056   T=128  32-row 76.1, 39.3*  128-row 79.7, 40.1   staged 99.7, 50.2
+//                             T=300  32-row 88.4, 48.8   128-row 87.0, 45.1*  staged 104, 53.9
+//                             T=777  32-row 159, 87.4    128-row 104, 60.9*   staged 158, 70.5
+// The Q8 64-row form spills. With most rows on a few experts the mean says too little: all on a quarter or an
+// eighth of the experts at means of 40 to 80 the staged tiles, which are then full, are the faster ones, by
+// up to 1.45 times on one launch (Q4 E=128 T=640 on 32 experts 64.9, 36.8 against 46.5, 31.0), where routing
+// by random logits gains as much (81.3, 51.1 against 113, 72.9) and a Zipf bias over the experts a fifth
+// (78.4, 45.4 against 99.5, 52.6).
 inline int moe_direct_rows(bool q4, bool swi, long M, long E, long cols) {
   const long mean = M / E;
   if (mean > (q4 ? 80 : 96)) return 0;
-  const int rows = mean <= (q4 ? 16 : 32) ? 32 : q4 && mean <= 48 ? 64 : 128;
+  // workgroups of the next height if every active expert had the mean
+  const int taller = q4 ? 64 : 128;
+  const long active = std::min(M, E);
+  const long items = active * ceil_div(M / active, taller) * moe_direct_tiles(taller, swi, cols);
+  int rows;
+  if (q4) {
+    const bool low = (mean <= 16 && M < 4096) || items < (mean <= 32 ? 256 : 128);
+    rows = low ? 32 : mean <= 48 ? 64 : 128;
+  } else {
+    const bool low = mean <= 20 || (mean <= 32 && items <= 384);
+    rows = low ? 32 : 128;
+  }
   // the staged tiles are larger, and so their grids smaller
-  const long items = moe_direct_groups(rows, M, std::min<long>(E, kMoeSlice)) * moe_direct_tiles(rows, swi, cols);
-  return grid_fits(items, 64 * moe_direct_waves(rows)) ? rows : 0;
+  const long grid = moe_direct_groups(rows, M, std::min<long>(E, kMoeSlice)) * moe_direct_tiles(rows, swi, cols);
+  return grid_fits(grid, 64 * moe_direct_waves(rows)) ? rows : 0;
 }
 
 }  // namespace qg

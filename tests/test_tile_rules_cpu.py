@@ -116,7 +116,26 @@ def test_dense_half_size_tiles_never_add_a_round(plans):
     assert seen == {(256, 128), (128, 256)}
 
 
-@pytest.mark.parametrize("q4,M,E,cols,swi", [(True, 65536, 4096, 494400, True), (True, 128, 128, (1 << 23) + 64, True),
+@pytest.mark.parametrize("q4,T,E,topk,hidden,inter,rows", [
+    # Q4: 32 rows up to a mean of 16 and below 4096 rows in all, 64 up to 48, 128 up to 80
+    (True, 4, 128, 8, 2048, 768, (32, 32)), (True, 256, 128, 8, 2048, 768, (32, 32)), (True, 272, 128, 8, 2048, 768, (64, 64)),
+    (True, 511, 256, 8, 4096, 2048, (32, 32)), (True, 512, 256, 8, 4096, 2048, (64, 64)), (True, 783, 128, 8, 2048, 768, (64, 64)), (True, 784, 128, 8, 2048, 768, (128, 128)),
+    (True, 1295, 128, 8, 2048, 768, (128, 128)), (True, 1296, 128, 8, 2048, 768, (0, 0)),
+    # and 32 rows on while 64 would leave CUs without a workgroup
+    (True, 128, 8, 2, 4096, 2048, (32, 32)), (True, 256, 16, 2, 1024, 512, (32, 32)), (True, 512, 16, 2, 1024, 512, (32, 32)),
+    (True, 128, 8, 2, 4096, 14336, (64, 32)),
+    (True, 2876, 64, 1, 896, 384, (64, 64)), (True, 160, 8, 2, 2048, 1984, (64, 32)), (True, 160, 8, 2, 2048, 1920, (32, 32)),
+    # Q8: 32 rows up to a mean of 20 (32 while 128 leaves CUs without a workgroup), 128 up to 96
+    (False, 128, 64, 6, 2048, 1056, (32, 32)), (False, 223, 64, 6, 2048, 1056, (32, 32)), (False, 224, 64, 6, 2048, 1056, (128, 128)), (False, 512, 128, 8, 2048, 768, (128, 128)),
+    (False, 192, 16, 2, 1024, 512, (32, 32)), (False, 300, 16, 2, 1024, 512, (128, 128)),
+    (False, 777, 64, 6, 2048, 1056, (128, 128)), (False, 1034, 64, 6, 2048, 1056, (128, 128)), (False, 1035, 64, 6, 2048, 1056, (0, 0))])
+def test_direct_rows(direct, q4, T, E, topk, hidden, inter, rows):
+    """Rows per group of the gate/up and the down projection."""
+    M = T * topk
+    assert tuple(r for r, _ in direct([(q4, M, E, inter, True), (q4, M, E, hidden, False)])) == rows
+
+
+@pytest.mark.parametrize("q4,M,E,cols,swi", [(False, 65536, 4096, 494400, True), (True, 128, 128, (1 << 23) + 64, True),
                                              (False, 128, 128, (1 << 24) + 128, False), (True, 4096, 128, 1 << 24, False)])
 def test_direct_grid_of_2_to_the_32_threads_is_left_to_the_staged_tiles(direct, q4, M, E, cols, swi):
     """The runtime counts a grid's threads in 32 bits: more of them wrap, and part of the output stays unwritten."""

@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -32,29 +33,29 @@ FLAGS = [
 
 
 def build(verbose: bool = False, extra=None) -> str:
-    """Compile every source (side by side, one object each) and link the library."""
-    objs = [os.path.splitext(src)[0] + ".o" for src in SOURCES]
-    cmds = [[HIPCC, *FLAGS, *(extra or []), "-c", src, "-o", obj] for src, obj in zip(SOURCES, objs)]
-    link = [HIPCC, f"--offload-arch={ARCH}", "-shared", *objs, "-o", LIB + ".tmp"]
-    if verbose:
-        for cmd in [*cmds, link]:
-            print(" ".join(cmd), flush=True)
-    procs = [subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for cmd in cmds]
-    outs = [p.communicate()[0] for p in procs]
-    rcs = [p.returncode for p in procs]
-    if not any(rcs):
-        res = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        outs.append(res.stdout)
-        rcs.append(res.returncode)
-    out = "\n".join(l for l in "".join(outs).splitlines() if "not a recognized feature" not in l)
-    for obj in objs:
-        if os.path.exists(obj):
-            os.remove(obj)
-    if any(rcs):
-        raise RuntimeError(f"hipcc failed ({rcs}):\n{out}")
-    if verbose and out.strip():
-        print(out)
-    os.replace(LIB + ".tmp", LIB)
+    """Compile every source (side by side, one object each) and link the library. All of it in a folder of
+    its own beside the library, which then replaces the old one in one step: builds may run at once."""
+    with tempfile.TemporaryDirectory(prefix="build-", dir=os.path.dirname(LIB)) as tmp:
+        objs = [os.path.join(tmp, os.path.basename(src) + ".o") for src in SOURCES]
+        new = os.path.join(tmp, os.path.basename(LIB))
+        cmds = [[HIPCC, *FLAGS, *(extra or []), "-c", src, "-o", obj] for src, obj in zip(SOURCES, objs)]
+        link = [HIPCC, f"--offload-arch={ARCH}", "-shared", *objs, "-o", new]
+        if verbose:
+            for cmd in [*cmds, link]:
+                print(" ".join(cmd), flush=True)
+        procs = [subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for cmd in cmds]
+        outs = [p.communicate()[0] for p in procs]
+        rcs = [p.returncode for p in procs]
+        if not any(rcs):
+            res = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+            outs.append(res.stdout)
+            rcs.append(res.returncode)
+        out = "\n".join(l for l in "".join(outs).splitlines() if "not a recognized feature" not in l)
+        if any(rcs):
+            raise RuntimeError(f"hipcc failed ({rcs}):\n{out}")
+        if verbose and out.strip():
+            print(out)
+        os.replace(new, LIB)
     return LIB
 
 

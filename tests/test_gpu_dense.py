@@ -63,10 +63,10 @@ RAGGED = [
     (255, 257, 288), (300, 1000, 32), (64, 64, 2048 + 32),
     (3857, 3684, 96),      # 256x256 tiles with ragged M and N tails
     (4096, 4096, 64),      # 256x256 tiles, exact
-    (300, 1000, 1536),     # split-K over 2 workgroups per 256x256 tile, ragged M and N
+    (300, 1000, 1536),     # split-K over 2 workgroups per 256x128 tile, ragged M and N
     (1000, 700, 4096 + 32),  # split-K over 5, K tail inside the last split
-    (512, 512, 8192),      # split-K over 8 on 128x256 tiles (the down-projection shape class)
-    (1500, 4000, 160),     # 128x256 tiles above 1024 rows (no split), ragged M and N
+    (512, 512, 8192),      # split-K over 8 on 256x128 tiles (the down-projection shape class)
+    (1500, 4000, 160),     # 256x128 tiles above 1024 rows (no split), ragged M and N
     (1100, 4352, 1056),    # the same with an odd K-step count and a K tail
 ]
 # every K-step count modulo the unrolled loop period (2 or 6 steps) and each K tail position,
@@ -110,7 +110,7 @@ def test_bitwise_deterministic_and_tile_independent(fmt):
     wq, sc = dev_w(torch, case.w)
     y1 = q.dense(x, wq, sc, fmt)        # 256x256 tiles
     y2 = q.dense(x, wq, sc, fmt)
-    y3 = q.dense(x[:200].contiguous(), wq, sc, fmt)   # 128x128 tiles
+    y3 = q.dense(x[:200].contiguous(), wq, sc, fmt)   # 128x256 tiles
     torch.cuda.synchronize()
     assert torch.equal(y1, y2)
     assert torch.equal(y1[:200], y3)

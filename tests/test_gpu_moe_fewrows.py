@@ -162,38 +162,52 @@ def test_small_groups_write_only_their_rows():
     check("moe_fewrows guard", x, r, ws, fmt, y.cpu().numpy(), 256)
 
 
-@pytest.mark.parametrize("fmt", FMTS)
-def test_tile_choice_boundary_bitwise(fmt):
-    """At most 32 rows per expert on average a launch takes 128x128 four-wave tiles, above that
-    192x256 eight-wave tiles. Both add the same MFMA products in the same K order, so a row routed
-    identically in a launch just below and one just above the boundary is bitwise equal; each
-    launch also meets the oracle's bar. Plain grouped GEMM and the fused gate/up + SiLU epilogue."""
+# Launches on either side of every limit of the tile choice: format, inter, K, (experts, rows) below and above,
+# and the rows per group there (0: staged tiles of 192 or 256 rows), the same for the gate/up and the plain GEMM
+LIMITS = [
+    (synth.FMT_Q4, 896, 416, (40, 679), (40, 680), 32, 64),        # mean 16 and 17
+    (synth.FMT_Q4, 128, 96, (255, 4095), (256, 4096), 32, 64),     # mean 16, below 4096 rows and not
+    (synth.FMT_Q4, 896, 96, (36, 720), (37, 720), 32, 64),         # 252 and 259 workgroups of 64 rows
+    (synth.FMT_Q4, 896, 96, (18, 720), (19, 720), 32, 64),         # mean 40 and 37, 126 and 133 of them
+    (synth.FMT_Q4, 896, 416, (40, 1959), (40, 1960), 64, 128),     # mean 48 and 49
+    (synth.FMT_Q4, 896, 416, (40, 3239), (40, 3240), 128, 0),      # mean 80 and 81
+    (synth.FMT_Q4, 128, 96, (4, 771), (4, 772), 0, 0),             # mean 192 and 193: 192 and 256 rows
+    (synth.FMT_Q8, 896, 416, (40, 839), (40, 840), 32, 128),       # mean 20 and 21
+    (synth.FMT_Q8, 896, 96, (27, 700), (28, 700), 32, 128),        # 378 and 392 workgroups of 128 rows
+    (synth.FMT_Q8, 896, 416, (24, 791), (24, 792), 32, 128),       # mean 32 and 33
+    (synth.FMT_Q8, 896, 416, (40, 3879), (40, 3880), 128, 0),      # mean 96 and 97
+]
+
+
+@pytest.mark.parametrize("fmt,inter,K,below,above,rows_below,rows_above", LIMITS)
+def test_tile_choice_boundary_bitwise(fmt, inter, K, below, above, rows_below, rows_above):
+    """All tiles and forms add the same MFMA products in the same K order, so a row routed identically in a
+    launch just below and one just above a limit of the tile choice is bitwise equal; each launch also meets
+    the oracle's bar. Plain grouped GEMM and the fused gate/up + SiLU epilogue. (That the launches take the
+    forms named is checked beside the rules themselves.)"""
     torch = torch_or_skip()
     m = q()
-    K, inter = 512, 128
-    counts = [32, 40, 20, 36]                       # 128 rows over 4 experts: mean 32
-    rng = synth.rng_for(28, fmt, *counts)
-    idx_a = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
-    rng.shuffle(idx_a)
-    idx_b = np.concatenate([idx_a, np.zeros(4, np.int32)])   # 132 rows: mean 33
+    rng = synth.rng_for(28, fmt, inter, K, *below, *above)
+    kinds = 4                                           # experts share four weight matrices
+    idx_b = (below[0] * rng.random(above[1]) ** 1.5).astype(np.int32)
     x_b = synth.make_x(rng, idx_b.size, K)
-    x_a = np.ascontiguousarray(x_b[:idx_a.size])
-    ws = [synth.make_qweight(rng, 2 * inter, K, fmt) for _ in counts]
-    wq, sc = dev_experts(torch, ws)
-    table = m.ExpertTable(wq, sc, fmt)
+    ws4 = [synth.make_qweight(rng, 2 * inter, K, fmt) for _ in range(kinds)]
+    wq4, sc4 = dev_experts(torch, ws4)
     ys, hs = [], []
-    for x, idx in ((x_a, idx_a), (x_b, idx_b)):
-        r = synth.routing_from_idx(idx, len(counts), 1, np.ones(idx.size, np.float32))
+    for E, n in (below, above):
+        x, idx = np.ascontiguousarray(x_b[:n]), idx_b[:n]
+        table = m.ExpertTable([wq4[e % kinds] for e in range(E)], [sc4[e % kinds] for e in range(E)], fmt)
+        r = synth.routing_from_idx(idx, E, 1, np.ones(n, np.float32))
         off = dev_i32(torch, r.expert_offsets)
         perm = m.moe_bucket(dev_i32(torch, r.token_expert_idx), off)
         y = m.moe_grouped(dev_x(torch, x), perm, off, table, None, 1, fmt)
         h = m.moe_gate_up_swiglu(dev_x(torch, x), perm, off, table, None, 1, fmt)
         torch.cuda.synchronize()
-        y = y.cpu().numpy()
-        check(f"moe tile boundary rows={idx.size} {synth.FMT_NAMES[fmt]}", x, r, ws, fmt, y, K)
-        ys.append(y)
+        ys.append(y.cpu().numpy())
         hs.append(h.cpu().view(torch.int16).numpy().view(np.uint16))
-    n = idx_a.size
+    r4 = synth.routing_from_idx(idx_b % kinds, kinds, 1, np.ones(idx_b.size, np.float32))
+    check(f"moe tile boundary {below} {above} {synth.FMT_NAMES[fmt]}", x_b, r4, ws4, fmt, ys[1], K)
+    n = below[1]
     assert np.array_equal(ys[0].view(np.uint32), ys[1][:n].view(np.uint32))
     assert np.array_equal(hs[0], hs[1][:n])
 
@@ -205,8 +219,8 @@ def test_small_groups_in_eight_wave_launches_bitwise(fmt, inter, K):
     expert, in launches of 256x256 tiles (1544 rows over 8 experts: mean 193; 900 = 3 x 256 + 132,
     541 = 2 x 256 + 29) and of 192x256 tiles (the same routing over 9 experts: mean 171; 900 =
     4 x 192 + 132, 541 = 2 x 192 + 157). Plain and fused SwiGLU results meet the oracle's bar and
-    are bitwise equal to the same routing over 49 experts (mean 31), which takes the four-wave
-    tiles. inter = 384 gives three 256-column tiles (plain and gate/up), an odd count; K = 160 ends
+    are bitwise equal to the same routing over 49 experts (mean 31), which takes the direct
+    kernel's 32-row groups. inter = 384 gives three 256-column tiles (plain and gate/up), an odd count; K = 160 ends
     in half a K step."""
     torch = torch_or_skip()
     m = q()

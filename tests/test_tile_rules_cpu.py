@@ -8,10 +8,13 @@ for the tile's shape alone.
 import os
 import random
 import subprocess
+import sys
 
 import pytest
 
 from paper_2607_19438_amd import build
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 
 MAIN = """
 #include <cstdio>
@@ -142,3 +145,19 @@ def test_direct_grid_of_2_to_the_32_threads_is_left_to_the_staged_tiles(direct, 
     assert direct([(q4, M, E, cols, swi)])[0][0] == 0
     (rows, groups), = direct([(q4, M, E, cols // 8, swi)])
     assert rows > 0 and 0 < groups * 64 * (8 if rows == 64 else 4) < 1 << 32
+
+
+def test_direct_limits_that_the_gpu_tests_straddle(direct):
+    import test_gpu_moe_direct as forms
+    import test_gpu_moe_fewrows as few
+    for fmt, inter, _, below, above, rows_below, rows_above in few.LIMITS:
+        for (E, M), rows in ((below, rows_below), (above, rows_above)):
+            q4 = fmt == few.synth.FMT_Q4
+            got = direct([(q4, M, E, inter, True), (q4, M, E, 2 * inter, False)])
+            assert [r for r, _ in got] == [rows, rows], (fmt, E, M)
+    for fmt, rows in forms.FORMS.items():
+        q4 = fmt == few.synth.FMT_Q4
+        M, E = 4 * sum(forms.COUNTS), [4 * e for e in forms.EXPERTS]
+        for inter in (130, 168):
+            assert [direct([(q4, M, e, inter, True)])[0][0] for e in E] == rows
+            assert [direct([(q4, M, e, 2 * inter, False)])[0][0] for e in E] == rows

@@ -104,28 +104,35 @@ def test_empty_experts_never_read():
     assert np.isfinite(y).all()
 
 
-def test_inconsistent_routing_is_reported(monkeypatch):
-    """Offsets that disagree with the expert ids: the rows concerned become NaN; validation reports it."""
+# one workgroup, the largest that it takes, and the two-kernel bucketing; K and N as short as they get for the last
+@pytest.mark.parametrize("T,N,K", [(40, 128, 64), (4096, 36, 32), (4100, 36, 32)])
+def test_inconsistent_routing_is_reported(monkeypatch, T, N, K):
+    """Offsets that disagree with the expert ids, and an id out of range: the rows concerned become NaN;
+    validation reports either."""
     torch = torch_or_skip()
-    T, E, N, K = 40, 4, 128, 64
-    idx = np.array([0, 1, 2, 3] * 10, np.int32)
+    E = 4
+    idx = np.array([0, 1, 2, 3] * (T // 4), np.int32)
     x, r, ws = small_case(7, T, E, 1, N, K, synth.FMT_Q8, idx=idx)
     bad = r.expert_offsets.copy()
     bad[2] += 1                                   # experts 1 and 2 now disagree with their counts
+    ids = idx.copy()
+    ids[T // 8 * 4 + 3] = E                       # an id past the last expert, so expert 3 is one short
     xd = dev_x(torch, x)
     wq, sc = dev_experts(torch, ws)
-    y = q().moe(xd, dev_i32(torch, idx), dev_i32(torch, bad), wq, sc, 1, synth.FMT_Q8)
-    torch.cuda.synchronize()
-    yh = y.cpu().numpy()
-    assert np.isnan(yh[idx == 1]).all() and np.isnan(yh[idx == 2]).all()
     yr, b = oracle.moe(x, idx, r.expert_offsets, [w.wq for w in ws], [w.scales for w in ws], 1, synth.FMT_Q8,
                        bf16_weights=True)
-    good = (idx == 0) | (idx == 3)
-    assert np.all(np.abs(yh[good] - yr[good]) <= oracle.fp32_sum_rel(K) * b[good])
+    for i, off, lost in ((idx, bad, (1, 2)), (ids, r.expert_offsets, (3,))):
+        y = q().moe(xd, dev_i32(torch, i), dev_i32(torch, off), wq, sc, 1, synth.FMT_Q8)
+        torch.cuda.synchronize()
+        yh = y.cpu().numpy()
+        out = np.isin(idx, lost)                  # the row with the bad id is one of expert 3's
+        assert np.isnan(yh[out]).all()
+        assert np.all(np.abs(yh[~out] - yr[~out]) <= oracle.fp32_sum_rel(K) * b[~out])
     monkeypatch.setenv("QGEMM_VALIDATE", "1")
-    with pytest.raises(q().QGemmError):
-        q().moe(xd, dev_i32(torch, idx), dev_i32(torch, bad), wq, sc, 1, synth.FMT_Q8)
-    q().moe(xd, dev_i32(torch, idx), dev_i32(torch, r.expert_offsets), wq, sc, 1, synth.FMT_Q8)
+    for i, off in ((idx, bad), (ids, r.expert_offsets)):
+        with pytest.raises(q().QGemmError):
+            q().moe(xd, dev_i32(torch, i), dev_i32(torch, off), wq, sc, 1, synth.FMT_Q8)
+        q().moe(xd, dev_i32(torch, idx), dev_i32(torch, r.expert_offsets), wq, sc, 1, synth.FMT_Q8)
 
 
 @pytest.mark.parametrize("T,topk", [(1024, 8), (3200, 8), (4200, 6)])

@@ -77,7 +77,17 @@ int launch_dense(const qg::TileArgs& a, const void* wq, const void* sc, hipStrea
 std::mutex g_split_mutex;
 std::vector<std::pair<float*, size_t>> g_split_ws;
 
-int split_workspace(size_t floats, float** out) {
+bool may_allocate(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+// The workspace, of at least `floats`. A call leaves `keep` floats of it behind, what the finest split of its
+// sizes would take, also where a coarser one or none is faster: a later call inside a graph capture cannot
+// allocate, and a growth after a capture would free what the graph uses. Only `floats` is an error to lack.
+int split_workspace(size_t floats, size_t keep, hipStream_t s, float** out) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) {
     (void)hipGetLastError();
@@ -85,21 +95,23 @@ int split_workspace(size_t floats, float** out) {
   }
   if ((int)g_split_ws.size() <= dev) g_split_ws.resize(dev + 1, {nullptr, 0});
   auto& w = g_split_ws[dev];
-  if (w.second < floats) {
+  if (w.second < floats || (w.second < keep && may_allocate(s))) {
     if (w.first) (void)hipFree(w.first);   // waits for work that may still use it
     w = {nullptr, 0};
-    if (hipMalloc(reinterpret_cast<void**>(&w.first), floats * sizeof(float)) != hipSuccess) {
+    for (const size_t n : {std::max(floats, keep), floats}) {
+      if (hipMalloc(reinterpret_cast<void**>(&w.first), n * sizeof(float)) == hipSuccess) {
+        w.second = n;
+        break;
+      }
       (void)hipGetLastError();
-      return fail(QGEMM_EHIP, "hipMalloc of %zu bytes for split-K partials failed", floats * sizeof(float));
+      w.first = nullptr;
     }
-    w.second = floats;
+    if (w.second < floats)
+      return fail(QGEMM_EHIP, "hipMalloc of %zu bytes for split-K partials failed", floats * sizeof(float));
   }
   *out = w.first;
   return QGEMM_OK;
 }
-
-constexpr long kSmTargetGroups = 256;   // workgroups (of eight waves) to fill the CUs without a K split
-constexpr int kSmMaxJW = 8;             // chunks per wave held in registers
 
 template <int FMT, int JW, int MT>
 int launch_small(const qg::SmallArgs& a, long groups, hipStream_t s) {
@@ -118,35 +130,13 @@ int launch_small_jw(const qg::SmallArgs& a, int JW, long groups, hipStream_t s) 
   }
 }
 
-// M <= 16 (or up to 128 in MT blocks of 16 columns): 32 weight rows per workgroup; K is split over
-// workgroups only when there are fewer than 256 row blocks (or a wave would hold more than kSmMaxJW
-// chunks) and K is longer than small_unsplit_k. Split partials go to the split-K workspace and a
-// second kernel adds them in split order: a dependent launch (about 2 us) and a partial per output and
-// workgroup, so a short K is faster in one workgroup's hands and a long one in few. One block: about
-// 1024 of K to a workgroup (two Q8 chunks or one Q4 chunk per wave); two blocks 512; more blocks at
-// least 4 chunks, as their matrix work per chunk is larger. Measured in captured graphs, splits filling
-// 256 workgroups (with several blocks: of 4 chunks at least) against this rule (us):
-//   1 row     Q4 2048x2048 5.7 -> 4.7, 6000x2048 6.6 -> 5.1, 512x8192 8.0 -> 6.4; Q8 1000x512 6.0 -> 2.9,
-//             512x2048 7.6 -> 5.0, 300x2560 9.1 -> 5.6, 1500x4128 7.7 -> 6.8
-//   16 rows   Q4 1024x1024 6.9 -> 3.8, 7168x2048 8.2 -> 6.4; Q8 4096x2048 7.1 -> 6.6, 768x6144 10.3 -> 7.6
-//   24 rows   Q4 1024x1024 6.0 -> 4.6, Q8 2048x512 5.5 -> 3.8, 256x2048 6.7 -> 5.9 (unsplit 7.2)
-//   64 rows   Q8 1024x512 6.3 -> 5.1; unsplit at K = 1024 256 columns 7.1 against 6.3, 2048 7.1 against 7.6
-//   128 rows  Q8 1024x512 8.3 -> 7.2; unsplit at K = 1024 11.0 against 9.4
-constexpr int small_unsplit_k(int MT) { return MT == 1 ? 2048 : MT == 2 ? 1024 : 512; }
-
 template <int FMT>
 int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStream_t s) {
   using F = qg::SmallFmt<FMT>;
   const int MT = t.M <= 16 ? 1 : t.M <= 32 ? 2 : t.M <= 64 ? 4 : 8;
-  const long nc = (t.K + F::kKC - 1) / F::kKC;
   const long P = (t.N + qg::kSmRows - 1) / qg::kSmRows;
-  long S = std::min<long>(nc, (kSmTargetGroups + P - 1) / P);
-  if (t.K <= small_unsplit_k(MT)) S = 1;
-  else if (MT == 1) S = std::min<long>(S, (t.K + 1023) / 1024);
-  else S = std::min<long>(S, MT == 2 ? std::min<long>(nc / 4, (t.K + 511) / 512) : std::max<long>(1, nc / 4));
-  S = std::max<long>(S, (nc + qg::kSmWaves * kSmMaxJW - 1) / (qg::kSmWaves * kSmMaxJW));
-  const long cps = (nc + S - 1) / S;
-  S = (nc + cps - 1) / cps;
+  const qg::SmallPlan plan = qg::small_plan(MT, P, t.K, F::kKC);
+  const long S = plan.splits, cps = plan.cps;
   if (!qg::grid_fits(P * S, qg::kSmWaves * 64)) return fail(QGEMM_EUNSUPPORTED, "too many workgroups");
   int JW = 1;
   while (JW * qg::kSmWaves < cps) JW *= 2;
@@ -165,9 +155,9 @@ int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStr
   a.nbp_log2 = nbp_log2;
   std::unique_lock<std::mutex> lock(g_split_mutex, std::defer_lock);
   const long total = (long)t.M * t.N;
-  if (S > 1) {
+  if (plan.keep > 1) {
     lock.lock();
-    int rc = split_workspace((size_t)S * total, &a.ws);
+    int rc = split_workspace(S > 1 ? (size_t)S * total : 0, (size_t)plan.keep * total, s, &a.ws);
     if (rc != QGEMM_OK) return rc;
   }
   int rc;
@@ -188,13 +178,18 @@ int small_dispatch(const qg::TileArgs& t, const void* wq, const void* sc, hipStr
 // device-scope stores: Q4 512x8192x3072 40.1 -> 39.1 us, but Q4 768x1536x2048 22.6 -> 23.8, Q8
 // 300x5000x4096 28.7 -> 31.5 and 2048x2048x8192 83.9 -> 90.5, where few workgroups sum many partials.)
 template <int FMT, int BM, int BN>
-int launch_split(qg::TileArgs a, int S, const void* wq, const void* sc, hipStream_t s) {
-  if (S == 1) return launch_dense<FMT, BM, BN, 2, 4, 2>(a, wq, sc, s);
+int launch_split(qg::TileArgs a, const qg::DensePlan& plan, const void* wq, const void* sc, hipStream_t s) {
+  const int S = plan.splits;
   const long mn = (long)a.M * a.N;
-  std::lock_guard<std::mutex> lock(g_split_mutex);
+  std::unique_lock<std::mutex> lock(g_split_mutex, std::defer_lock);
   float* ws = nullptr;
-  int rc = split_workspace((size_t)S * mn, &ws);
-  if (rc != QGEMM_OK) return rc;
+  int rc = QGEMM_OK;
+  if (plan.keep > 1) {
+    lock.lock();
+    rc = split_workspace(S > 1 ? (size_t)S * mn : 0, (size_t)plan.keep * mn, s, &ws);
+    if (rc != QGEMM_OK) return rc;
+  }
+  if (S == 1) return launch_dense<FMT, BM, BN, 2, 4, 2>(a, wq, sc, s);
   a.ws = ws;
   a.splits = S;
   rc = launch_dense<FMT, BM, BN, 2, 4, 2>(a, wq, sc, s);
@@ -219,9 +214,9 @@ int dense_dispatch(qg::TileArgs a, const void* wq, const void* sc, hipStream_t s
   a.splits = 1;
   const qg::DensePlan plan = qg::dense_plan(FMT == qg::kQ4, a.M, a.N, a.K);
   switch (plan.tile) {
-    case qg::DenseTile::k256x256: return launch_split<FMT, 256, 256>(a, plan.splits, wq, sc, s);
-    case qg::DenseTile::k256x128: return launch_split<FMT, 256, 128>(a, plan.splits, wq, sc, s);
-    case qg::DenseTile::k128x256: return launch_split<FMT, 128, 256>(a, plan.splits, wq, sc, s);
+    case qg::DenseTile::k256x256: return launch_split<FMT, 256, 256>(a, plan, wq, sc, s);
+    case qg::DenseTile::k256x128: return launch_split<FMT, 256, 128>(a, plan, wq, sc, s);
+    case qg::DenseTile::k128x256: return launch_split<FMT, 128, 256>(a, plan, wq, sc, s);
     case qg::DenseTile::k128x128: break;
   }
   return launch_dense<FMT, 128, 128, 2, 2, 2>(a, wq, sc, s);

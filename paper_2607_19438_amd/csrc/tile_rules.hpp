@@ -11,6 +11,7 @@ enum class DenseTile { k256x256, k256x128, k128x256, k128x128 };
 struct DensePlan {
   DenseTile tile;
   int splits;      // workgroups that share a tile's K
+  int keep;        // splits that the workspace of partials is to hold, at least those
 };
 
 constexpr int kMinStepsPerSplit = 12;
@@ -55,12 +56,12 @@ inline int k_splits(long most, long nk) {
 inline DensePlan dense_plan(bool q4, long M, long N, long K) {
   const long nk = ceil_div(K, 64);
   const long big = ceil_div(M, 256) * ceil_div(N, 256);
-  if (M >= 256 && N >= 256 && big >= 200) return {DenseTile::k256x256, 1};
+  if (M >= 256 && N >= 256 && big >= 200) return {DenseTile::k256x256, 1, 1};
   const bool vec = M * N % 4 == 0;         // the partials are summed four at a time
   if (M >= 128 && M <= 2048 && N >= 256 && vec) {
     const long wide = ceil_div(M, 128) * ceil_div(N, 256);
     const int ws = k_splits(256 / wide, nk);
-    if (M < 256) return {DenseTile::k128x256, ws};
+    if (M < 256) return {DenseTile::k128x256, ws, ws};
     const long tall = ceil_div(M, 256) * ceil_div(N, 128);
     const int ts = k_splits(256 / tall, nk);
     auto cost = [&](long tiles, int S, double step) {
@@ -68,15 +69,61 @@ inline DensePlan dense_plan(bool q4, long M, long N, long K) {
       return ceil_div(tiles * S, 256) * ceil_div(nk, S) * step + sums;
     };
     if (M <= 1024 || tall > 128 || (wide > 128 && ts > 1)) {
-      if (cost(tall, ts, 1.0) <= cost(wide, ws, q4 ? 1.3 : 1.5)) return {DenseTile::k256x128, ts};
-      return {DenseTile::k128x256, ws};
+      // a call on 256x128 tiles also keeps what the splits of the other tiles would take
+      const int other = M <= 1024 || wide > 128 ? ws : k_splits(ceil_div(256, big), nk);
+      if (cost(tall, ts, 1.0) <= cost(wide, ws, q4 ? 1.3 : 1.5)) return {DenseTile::k256x128, ts, std::max(ts, other)};
+      return {DenseTile::k128x256, ws, std::max(ws, other)};
     }
   }
   if (M >= 256 && N >= 256 && vec) {
     const int S = k_splits(ceil_div(256, big), nk);
-    if (S > 1) return {DenseTile::k256x256, S};
+    if (S > 1) return {DenseTile::k256x256, S, S};
   }
-  return {DenseTile::k128x128, 1};
+  return {DenseTile::k128x128, 1, 1};
+}
+
+struct SmallPlan {
+  long splits;     // workgroups along K per 32-row block
+  long cps;        // chunks of K per split
+  long keep;       // splits that the workspace of partials is to hold, at least those
+};
+
+constexpr long kSmTargetGroups = 256;   // workgroups (of eight waves) to fill the CUs without a K split
+constexpr int kSmChunks = 8 * 8;        // chunks that a workgroup's eight waves hold in registers at most
+
+// The small-M kernel (qgemm_smallm.hpp) for MT column blocks, P row blocks and K in chunks of kc.
+//
+// M <= 16 (or up to 128 in MT blocks of 16 columns): 32 weight rows per workgroup; K is split over
+// workgroups only when there are fewer than 256 row blocks (or a wave would hold more than eight
+// chunks) and K is longer than small_unsplit_k. Split partials go to the split-K workspace and a
+// second kernel adds them in split order: a dependent launch (about 2 us) and a partial per output and
+// workgroup, so a short K is faster in one workgroup's hands and a long one in few. One block: about
+// 1024 of K to a workgroup (two Q8 chunks or one Q4 chunk per wave); two blocks 512; more blocks at
+// least 4 chunks, as their matrix work per chunk is larger. Measured in captured graphs, splits filling
+// 256 workgroups (with several blocks: of 4 chunks at least) against this rule (us):
+//   1 row     Q4 2048x2048 5.7 -> 4.7, 6000x2048 6.6 -> 5.1, 512x8192 8.0 -> 6.4; Q8 1000x512 6.0 -> 2.9,
+//             512x2048 7.6 -> 5.0, 300x2560 9.1 -> 5.6, 1500x4128 7.7 -> 6.8
+//   16 rows   Q4 1024x1024 6.9 -> 3.8, 7168x2048 8.2 -> 6.4; Q8 4096x2048 7.1 -> 6.6, 768x6144 10.3 -> 7.6
+//   24 rows   Q4 1024x1024 6.0 -> 4.6, Q8 2048x512 5.5 -> 3.8, 256x2048 6.7 -> 5.9 (unsplit 7.2)
+//   64 rows   Q8 1024x512 6.3 -> 5.1; unsplit at K = 1024 256 columns 7.1 against 6.3, 2048 7.1 against 7.6
+//   128 rows  Q8 1024x512 8.3 -> 7.2; unsplit at K = 1024 11.0 against 9.4
+constexpr int small_unsplit_k(int MT) { return MT == 1 ? 2048 : MT == 2 ? 1024 : 512; }
+
+inline SmallPlan small_plan(int MT, long P, long K, long kc) {
+  const long nc = ceil_div(K, kc);
+  const long fill = std::min(nc, ceil_div(kSmTargetGroups, P));
+  const long few = MT == 1 ? fill : std::min(fill, std::max<long>(1, nc / 4));   // at least 4 chunks each
+  long S = few;
+  if (K <= small_unsplit_k(MT)) S = 1;
+  else if (MT == 1) S = std::min(S, ceil_div(K, 1024));
+  else if (MT == 2) S = std::min({fill, nc / 4, ceil_div(K, 512)});
+  auto even = [&](long s) {      // no part empty, none longer than the registers hold
+    const long cps = ceil_div(nc, std::max(s, ceil_div(nc, kSmChunks)));
+    return SmallPlan{ceil_div(nc, cps), cps, 0};
+  };
+  SmallPlan p = even(S);
+  p.keep = std::max(p.splits, even(few).splits);
+  return p;
 }
 
 // The direct MoE kernel (moe_direct.hpp): one 32-row block of weights per wave, `waves` of them and so

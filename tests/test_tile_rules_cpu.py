@@ -26,6 +26,12 @@ int main() {
     if (what == 'd') {
       const qg::DensePlan p = qg::dense_plan(q4 != 0, a, b, c);
       std::printf("%d %d\\n", (int)p.tile, p.splits);
+    } else if (what == 'k') {
+      const qg::DensePlan p = qg::dense_plan(q4 != 0, a, b, c);
+      std::printf("%d %d\\n", p.splits, p.keep);
+    } else if (what == 's') {
+      const qg::SmallPlan p = qg::small_plan(a <= 16 ? 1 : a <= 32 ? 2 : a <= 64 ? 4 : 8, (b + 31) / 32, c, q4 ? 128 : 64);
+      std::printf("%ld %ld\\n", p.splits, p.keep);
     } else {
       const int rows = qg::moe_direct_rows(q4 != 0, d != 0, a, b, c);
       std::printf("%d %ld\\n", rows, rows ? qg::moe_direct_groups(rows, a, b) * qg::moe_direct_tiles(rows, d != 0, c) : 0);
@@ -161,3 +167,47 @@ def test_direct_limits_that_the_gpu_tests_straddle(direct):
         for inter in (130, 168):
             assert [direct([(q4, M, e, inter, True)])[0][0] for e in E] == rows
             assert [direct([(q4, M, e, 2 * inter, False)])[0][0] for e in E] == rows
+
+
+def random_dense(rng, m_lo, m_hi, n):
+    out = []
+    while len(out) < n:
+        M, N, K = int(m_lo * (m_hi / m_lo) ** rng.random()), int(64 * 128 ** rng.random()), 32 * int(4 * 100 ** rng.random())
+        out.append((rng.random() < 0.5, M, N, K))
+    return out
+
+
+def test_small_workspace_holds_the_split_that_fills_the_chip(rules):
+    """A short K runs unsplit, but the call leaves the partials' workspace of the split over 256 workgroups, as a
+    later capture cannot allocate it."""
+    assert rules("s", [(True, 16, 2048, 2048), (False, 128, 1024, 512), (False, 1, 8192, 2048)]) == [(1, 4), (1, 2), (1, 1)]
+    calls = random_dense(random.Random(6), 1, 128, 2000)
+    fewer = 0
+    for (q4, M, N, K), (splits, keep) in zip(calls, rules("s", calls)):
+        nc = cd(K, 128 if q4 else 64)
+        S = min(nc, cd(256, cd(N, 32)))
+        if M > 16:
+            S = min(S, max(1, nc // 4))
+        S = max(S, cd(nc, 64))
+        assert 1 <= splits <= keep == max(splits, cd(nc, cd(nc, S))), (q4, M, N, K)
+        fewer += splits < keep
+    assert fewer > 200
+
+
+def test_dense_workspace_holds_the_splits_of_the_other_tiles(rules):
+    """256x128 tiles take fewer splits of K than the tiles that they replace; the workspace is sized for those."""
+    assert rules("k", [(True, 576, 1024, 4096), (False, 2048, 2048, 8192), (True, 1100, 7168, 2048)]) == [(5, 5), (4, 4), (1, 1)]
+    calls = random_dense(random.Random(7), 129, 4096, 4000)
+    fewer = 0
+    for (q4, M, N, K), (splits, keep) in zip(calls, rules("k", calls)):
+        big, wide, S = cd(M, 256) * cd(N, 256), cd(M, 128) * cd(N, 256), 1
+        if M * N % 4 == 0 and N >= 256 and not (M >= 256 and big >= 200):
+            if M <= 1024 or (M <= 2048 and wide > 128):
+                S = min(8, 256 // wide)
+            elif M >= 256:
+                S = min(8, cd(256, big))
+        while S > 1 and cd(K, 64) // S < 12:
+            S -= 1
+        assert keep == max(splits, S, 1), (q4, M, N, K)
+        fewer += splits < keep
+    assert fewer

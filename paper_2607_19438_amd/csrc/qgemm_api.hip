@@ -728,14 +728,7 @@ int qgemm_attention_prefill(const void* q, const void* k, const void* v, void* o
   if (causal != 0 && causal != 1) return fail(QGEMM_EINVAL, "causal must be 0 or 1 (got %d)", causal);
   if (!(scale > 0.0f) || !std::isfinite(scale)) return fail(QGEMM_EINVAL, "scale must be finite and > 0");
   if ((long)S * H * D > 0x7fffffffL) return fail(QGEMM_EUNSUPPORTED, "S*H*D must be below 2^31");
-  // Few workgroups: halve each one's rows and split a query's keys over two waves (attn_kernels.hpp).
-  // The line is where the split stops winning (512 workgroups of 128 rows are one round on 256 CUs):
-  // causal 512 x 32 heads (128 workgroups) 11.0 against 14.6 us, 2048 x 32 (512) 46.8 against 48.1 on one
-  // box and 47.6 against 46.6 on another, 4096 x 32 (1024) 155 against 142; without the mask all chains
-  // are equally long, 2 x 1000 x 16 (256) 14.8 against 15.8 us, 2048 x 32 (512) 77 against 67. With D = 64
-  // (four workgroups per CU) causal 3 x 700 x 32 (576) still takes 15.4 against 19.5 us.
-  const long work128 = (long)B * H * ((S + qg::kAttnBQ<false> - 1) / qg::kAttnBQ<false>);
-  const bool split = work128 <= (!causal ? 256 : D == 64 ? 640 : 400);
+  const bool split = qg::attn_split(D == 64, causal != 0, S, (long)B * H);
   const int bq = split ? qg::kAttnBQ<true> : qg::kAttnBQ<false>;
   const long nqb = (S + bq - 1) / bq;
   if (!qg::grid_fits((long)B * H * nqb, qg::kAttnThreads)) return fail(QGEMM_EUNSUPPORTED, "too many workgroups");

@@ -189,4 +189,33 @@ inline int moe_direct_rows(bool q4, bool swi, long M, long E, long cols) {
   return grid_fits(grid, 64 * moe_direct_waves(rows)) ? rows : 0;
 }
 
+// Prefill attention (attn_kernels.hpp) with few workgroups: whether each owns 64 query rows, not 128, and two
+// waves share a query's keys. That halves the chain of key blocks and doubles the workgroups, at more work per
+// block. Two workgroups fit a CU (four with D = 64), so it pays
+//   - up to one 64-row workgroup per CU; one key block has no chain to halve (S <= 64), and without the mask a
+//     second block of a few keys does not pay either;
+//   - up to two per CU where that many 128-row ones do not fit one per CU either, or where the chains are long
+//     enough; D = 64 up to four. The 64-row form takes the heaviest blocks of all heads first, dealt to the
+//     XCDs evenly only for a multiple of 8 heads: others stop earlier;
+//   - causal, D = 128: beyond that where the chains are long and uneven.
+// Measured, 128-row against 64-row (us, * the one taken; S x heads of all batches, a fourth as many key heads):
+//   D=128 causal  64 x 64 5.9*, 6.4  96 x 64 7.9, 6.6*  96 x 320 10.7*, 13.3  192 x 128 9.4*, 9.9  300 x 96 14.5, 11.3*
+//                 512 x 32 14.6, 11.7*  512 x 128 22.8*, 25.2  700 x 64 21.1*, 21.6  2048 x 16 39.2, 32.9*
+//   D=128 full    65 x 160 7.2*, 8.8  128 x 64 7.8, 7.1*  192 x 128 9.6*, 10.1  512 x 64 16.3, 16.1*  2048 x 32 69.2*, 79.9
+//   D=64  causal  96 x 256 6.5, 5.9*  96 x 640 9.1*, 10.5  300 x 192 12.7, 10.3*  1024 x 64 19.3, 18.6*
+// Over 1425 calls (32 to 2048 rows, 8 to 640 heads) 4 are more than 3% slower than 128 rows throughout, the worst
+// 6%, and the time is 0.939 of it on average; limits on the number of 128-row workgroups alone (causal 400, 640
+// with D = 64; full 256), without a look at S, made 217 of them slower, by up to 27%, and came to 0.953.
+inline bool attn_split(bool d64, bool causal, long S, long heads) {
+  const long wide = heads * ceil_div(S, 128), narrow = heads * ceil_div(S, 64);
+  const bool even = heads % 8 == 0;
+  if (S <= 64) return false;
+  if (!causal) return S > 72 && (S <= 450 ? narrow : wide) <= 256;
+  if (narrow <= 256) return true;
+  if (d64) return narrow <= (S <= 128 ? 768 : S <= 320 || (!even && S > 600) ? 1024 : even ? 1200 : 600);
+  if (wide > 256)
+    return narrow <= 528 || (S > 600 && even && wide <= 320) || (S >= 900 && wide <= (S < 1200 ? 384 : 400));
+  return (S > 128 && S <= 160) || (S > 192 && (even || S > 600 || narrow <= 400));
+}
+
 }  // namespace qg

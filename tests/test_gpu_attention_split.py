@@ -9,13 +9,15 @@ from gpu_util import torch_or_skip
 
 pytestmark = pytest.mark.gpu
 
-SPLIT = [(1, S, 3, 3, D) for S in (31, 32, 33, 63, 65, 95, 96, 97, 161) for D in (64, 128)]
-# more than 400 (causal, 640 with D = 64) and 256 workgroups of 128 rows; the last one at the limit
-MANY = [(9, 130, 36, 4, 128), (9, 130, 36, 4, 64), (5, 129, 66, 11, 64), (5, 257, 27, 3, 128), (5, 129, 64, 8, 64)]
+SPLIT_BOTH = [(1, S, 3, 3, D) for S in (73, 95, 96, 97, 127, 161) for D in (64, 128)]   # with and without the mask
+SPLIT = SPLIT_BOTH + [(1, S, 3, 3, D) for S in (31, 32, 33, 63, 64, 65) for D in (64, 128)]   # split from 65 on if causal
+# too many workgroups to split, and at a limit with the mask (split)
+MANY = [(9, 130, 36, 4, 128), (10, 130, 36, 4, 64), (5, 129, 72, 12, 64), (5, 257, 27, 3, 128)]
+LIMIT = [(9, 130, 36, 4, 64), (5, 129, 66, 11, 64), (5, 129, 64, 8, 64), (2, 129, 88, 11, 128), (8, 300, 12, 3, 128)]
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,H,Hkv,D", SPLIT + MANY)
+@pytest.mark.parametrize("B,S,H,Hkv,D", SPLIT + MANY + LIMIT)
 def test_attention_forms(B, S, H, Hkv, D, causal):
     torch = torch_or_skip()
     case = synth.attn_case(f"attn_forms_{B}x{S}x{H}/{Hkv}x{D}_{'c' if causal else 'f'}", B, S, H, Hkv, D, causal,
@@ -25,7 +27,7 @@ def test_attention_forms(B, S, H, Hkv, D, causal):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,H,Hkv,D", [(1, 40, 3, 3, 64), (1, 97, 3, 3, 128), (5, 129, 66, 11, 64), (9, 130, 36, 4, 128)])
+@pytest.mark.parametrize("B,S,H,Hkv,D", [(1, 40, 3, 3, 64), (1, 97, 3, 3, 64), (1, 97, 3, 3, 128), (5, 129, 66, 11, 64), (9, 130, 36, 4, 128)])
 def test_attention_keys_scoring_minus_infinity(B, S, H, Hkv, D, causal):
     """Keys 32..63 score -inf for every query (their first element is -inf, the queries' is positive): they
     take no weight in either form, also where they are all that one of two waves has seen."""

@@ -29,6 +29,8 @@ int main() {
     } else if (what == 'k') {
       const qg::DensePlan p = qg::dense_plan(q4 != 0, a, b, c);
       std::printf("%d %d\\n", p.splits, p.keep);
+    } else if (what == 'a') {
+      std::printf("%d 0\\n", (int)qg::attn_split(q4 != 0, a != 0, b, c));
     } else if (what == 's') {
       const qg::SmallPlan p = qg::small_plan(a <= 16 ? 1 : a <= 32 ? 2 : a <= 64 ? 4 : 8, (b + 31) / 32, c, q4 ? 128 : 64);
       std::printf("%ld %ld\\n", p.splits, p.keep);
@@ -211,3 +213,26 @@ def test_dense_workspace_holds_the_splits_of_the_other_tiles(rules):
         assert keep == max(splits, S, 1), (q4, M, N, K)
         fewer += splits < keep
     assert fewer
+
+
+@pytest.mark.parametrize("D,causal,S,heads,split", [
+    # one key block, or a second one of a few keys: nothing to halve
+    (128, True, 64, 64, 0), (64, False, 64, 8, 0), (128, True, 65, 64, 1), (128, False, 72, 64, 0), (128, False, 73, 64, 1),
+    # one 64-row workgroup per CU, and one head more
+    (128, False, 96, 128, 1), (128, False, 96, 129, 0), (128, True, 96, 128, 1), (128, True, 96, 136, 0), (64, True, 96, 136, 1),
+    # two (four) per CU
+    (128, True, 300, 96, 1), (128, True, 300, 120, 0), (128, True, 192, 128, 0), (128, True, 512, 64, 1), (128, True, 512, 62, 0),
+    (128, False, 512, 64, 1), (128, False, 512, 72, 0), (64, True, 96, 384, 1), (64, True, 96, 392, 0), (64, True, 300, 204, 1),
+    # long causal chains
+    (128, True, 700, 48, 1), (128, True, 700, 64, 0), (128, True, 1024, 48, 1), (128, True, 2048, 25, 1), (128, True, 2048, 32, 0),
+    (64, True, 2048, 32, 1), (64, True, 4096, 32, 0)])
+def test_attention_split(rules, D, causal, S, heads, split):
+    assert rules("a", [(D == 64, causal, S, heads)]) == [(split, 0)]
+
+
+def test_attention_forms_that_the_gpu_tests_name(rules):
+    import test_gpu_attention_split as forms
+    for cases, split in ((forms.SPLIT_BOTH, 1), (forms.MANY, 0)):
+        for B, S, H, _, D in cases:
+            for causal in (False, True):
+                assert rules("a", [(D == 64, causal, S, B * H)]) == [(split, 0)], (B, S, H, D, causal)

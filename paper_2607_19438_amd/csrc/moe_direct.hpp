@@ -10,13 +10,14 @@
 // v_mfma_f32_32x32x16_bf16, and multiplies with the group's activation rows, which the workgroup's
 // waves share through LDS (DMA, double-buffered, one barrier per stage).
 //
-// What bounds it (Q4, MI355X): a K sub-step of a wave is ~84 VALU instructions (68 of them the
-// dequantisation of 32 weights per lane) and 4 MFMAs per 32 rows; a SIMD issues about one VALU
-// instruction per 4.3 cycles with several waves resident, so T=16 (81 active experts) needs ~23 us
-// of issue and 27 us of HBM at the copy rate for its gate/up launch, which takes 44 us (staged tiles
-// 69). With every expert reading the same weights it takes 27 us. Loading a stage's weights at once
-// instead of refilling each register as it is used: T=16 47.6 -> 44.2 us, T=128 75 -> 67 us (the
-// four loads of a 128-byte line reach the vector L1 together).
+// What bounds it (MI355X): no single unit. Counters of the gate/up launches (E=128 2048/768 Q4, E=64 2048/1056
+// Q8): T=128 Q4 VALU busy 40%, MFMA 13%, LDS 7%, 139 MB fetched at 3.4 TB/s (a large copy reaches 5.2), waves
+// 39% of their time in waits; T=4 Q4 24%, 8%, 4%, 2.5 TB/s, 52% (at most 1.5 four-wave workgroups per CU); T=777
+// Q8 26%, 19%, 10%, 3.6 TB/s, 45% (two waves per SIMD). A K sub-step of a wave is ~84 VALU instructions (68 of
+// them the dequantisation of 32 weights per lane) and 4 MFMAs per 32 rows, and a stage ends in a barrier, so the
+// weight stream and the arithmetic overlap only as far as the few waves of a SIMD are at different places.
+// Loading a stage's weights at once instead of refilling each register as it is used: T=16 gate/up 47.6 ->
+// 44.2 us, T=128 75 -> 67 us (the four loads of a 128-byte line reach the vector L1 together).
 //
 // The MFMAs add the same products in the same K order as the staged tiles, so a row's result is
 // bitwise the same whichever kernel computes it.

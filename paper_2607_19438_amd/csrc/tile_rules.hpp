@@ -164,11 +164,12 @@ inline long moe_direct_groups(int rows, long M, long experts) {
 //   Q8 E=64 top-6 2048/1056   T=128  32-row 76.1, 39.3*  128-row 79.7, 40.1   staged 99.7, 50.2
 //                             T=300  32-row 88.4, 48.8   128-row 87.0, 45.1*  staged 104, 53.9
 //                             T=777  32-row 159, 87.4    128-row 104, 60.9*   staged 158, 70.5
-// The Q8 64-row form spills. With most rows on a few experts the mean says too little: all on a quarter or an
-// eighth of the experts at means of 40 to 80 the staged tiles, which are then full, are the faster ones, by
-// up to 1.45 times on one launch (Q4 E=128 T=640 on 32 experts 64.9, 36.8 against 46.5, 31.0), where routing
-// by random logits gains as much (81.3, 51.1 against 113, 72.9) and a Zipf bias over the experts a fifth
-// (78.4, 45.4 against 99.5, 52.6).
+// The Q8 64-row form is left out: it spills 41 (gate/up) and 37 (down) of its 128 VGPRs, the 32-row one 4 and
+// 5. With most rows on a few experts the mean says too little: all on a quarter or an eighth of the experts at
+// means of 40 to 80 the staged tiles, which are then full, are the faster ones, by up to 1.45 times on one
+// launch (Q4 E=128 T=640 on 32 experts 64.9, 36.8 against 46.5, 31.0), where routing by random logits gains as
+// much (81.3, 51.1 against 113, 72.9) and a Zipf bias over the experts a fifth (78.4, 45.4 against 99.5, 52.6).
+// With top-1 a Zipf bias concentrates enough to lose, too (Q4 E=96 2368/1184 T=3746 152 together against 132).
 inline int moe_direct_rows(bool q4, bool swi, long M, long E, long cols) {
   const long mean = M / E;
   if (mean > (q4 ? 80 : 96)) return 0;
